@@ -67,7 +67,9 @@
  * takes for its sizes; the call takes `workspace` (16-byte aligned, not
  * overlapping any other buffer of the call; may be NULL when the size is 0)
  * and its size `workspace_bytes`, and returns GSPN_ERR_WORKSPACE when it is
- * smaller than needed.  The workspace's contents on entry do not matter and
+ * smaller than needed.  Planes above 64 take the size given for their fastest
+ * plan and run with less too, in smaller parts (the same results bit for bit)
+ * or, below what a part takes, on slower kernels.  The workspace's contents on entry do not matter and
  * are undefined after the call; calls that share a workspace must not run
  * concurrently.
  *
@@ -126,7 +128,8 @@ extern "C" {
 /*
  * Bytes of workspace that operation `op` (GSPN_OP_*) takes for these sizes,
  * in *bytes (0 for most shapes).  The same argument checks as the call; the
- * plan of a call is the same for every call with these sizes on one device.
+ * plan of a call is the same for every call with these sizes and at least
+ * this workspace on one device.
  * Needs the current device (GSPN_ERR_HIP without one).
  */
 int gspn_workspace_size(int op, int direction, int B, int C, int G, int H, int W, int dtype,

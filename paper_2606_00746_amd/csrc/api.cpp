@@ -94,6 +94,8 @@ hipError_t dispatch_fwd(const Problem &p, hipStream_t s)
         return launch_fwd_small(p, s);
     if (wide_supported(p))
         return launch_fwd_wide(p, s);
+    if (line_supported(p, false))
+        return launch_fwd_line(p, s);
     return launch_fwd_general(p, s);
 }
 
@@ -105,6 +107,8 @@ hipError_t dispatch_bwd(const Problem &p, hipStream_t s)
         return launch_bwd_tiny(p, s);
     if (p.H <= kSmallSide && p.W <= kSmallSide)
         return launch_bwd_small(p, s);
+    if (line_supported(p, true))
+        return launch_bwd_line(p, s);
     return launch_bwd_general(p, s);
 }
 
@@ -238,6 +242,19 @@ int count_workspace(int op, const Problem &p0, int64_t *bytes, int64_t *reserve_
     return GSPN_OK;
 }
 
+// The plan of a call with `given` bytes of workspace: the one the query sizes,
+// or, where that needs more, the one p.ws_cap leaves (the same unless the
+// family can do with less).
+int plan_workspace(int op, Problem &p, int64_t given, int64_t *need, int64_t *rneed = nullptr)
+{
+    int st = count_workspace(op, p, need, rneed);
+    if (st == GSPN_OK && *need > given) {
+        p.ws_cap = given;
+        st = count_workspace(op, p, need, rneed);
+    }
+    return st;
+}
+
 int scan_call(int op, const void *x, const void *w, const void *lam, const void *u, const void *dy,
               void *y, void *dx, void *dw, void *dlam, void *du, int direction, int B, int C,
               int G, int H, int W, int dtype, void *workspace, int64_t workspace_bytes,
@@ -258,12 +275,12 @@ int scan_call(int op, const void *x, const void *w, const void *lam, const void 
     const bool blocked = op == GSPN_OP_FWD_BLOCKED || op == GSPN_OP_BWD_BLOCKED;
     Problem p{x, w, lam, u, dy, y, dx, dw, dlam, du, direction, B, C, G, H, W, dtype,
               blocked ? kBlocked : kPixelMajor, nullptr, slots};
-    int64_t need = 0, rneed = 0;
-    st = count_workspace(op, p, &need, &rneed);
-    if (st != GSPN_OK)
-        return st;
     if (workspace_bytes < 0 || reserve_bytes < 0)
         return GSPN_ERR_WORKSPACE;
+    int64_t need = 0, rneed = 0;
+    st = plan_workspace(op, p, workspace_bytes, &need, &rneed);
+    if (st != GSPN_OK)
+        return st;
     if (rneed > 0) {
         // written by the forward of a training pair, read by its backward
         if (reserve == nullptr || reserve_bytes < rneed)
@@ -542,7 +559,7 @@ extern "C" int gspn_scan_bwd_static(const void *x, const void *w, const void *la
     Problem p{x, w, lam, u, dy, nullptr, dx, dw, dlam, du, direction, B, C, G, H, W, dtype,
               kPixelMajor, nullptr};
     int64_t need = 0;
-    st = count_workspace(GSPN_OP_BWD, p, &need);
+    st = plan_workspace(GSPN_OP_BWD, p, (int64_t)kStaticScratchBytes, &need);
     if (st != GSPN_OK)
         return st;
     if (need > (int64_t)kStaticScratchBytes)

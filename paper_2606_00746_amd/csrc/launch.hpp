@@ -64,6 +64,11 @@ struct Problem {
     Workspace *rs = nullptr;
     bool rs_write = false, rs_read = false;
     const ReserveParts *rsp = nullptr;
+    // the caller's workspace bytes where they are fewer than the size the
+    // query gives (a fixed workspace, one sized for less): families that can
+    // do with less choose their plan by it, and a call that needs more than
+    // this is refused; < 0: the plan the query sizes
+    int64_t ws_cap = -1;
 };
 
 // Takes the reserve's parts from p.rs.  Weights the library forms itself
@@ -136,8 +141,15 @@ hipError_t launch_fwd_pm(const Problem &p, hipStream_t s);
 // launch_norm and the re-layout of launch_w_to_blocked in one pass.
 hipError_t launch_norm_blocked(const Problem &p, const void *wt, void *wb, hipStream_t s);
 hipError_t launch_fwd_wide(const Problem &p, hipStream_t s);
+// Planes of any type and layout with both sides up to kLineSide (scan_line.hip).
+constexpr int kLineSide = 256;
+bool line_supported(const Problem &p, bool bwd);
+hipError_t launch_fwd_line(const Problem &p, hipStream_t s);
+hipError_t launch_bwd_line(const Problem &p, hipStream_t s);
 hipError_t launch_fwd_general(const Problem &p, hipStream_t s);
 hipError_t launch_bwd_general(const Problem &p, hipStream_t s);
+int64_t general_fwd_bytes(const Problem &p);
+int64_t general_bwd_bytes(const Problem &p);
 
 // 1x1 convolutions of the latent sublayer (bf16, fp32 accumulation):
 // y[b] = a x[b] with a [M][K], x [B][K][H*W], y [B][M][H*W]; and the

@@ -195,7 +195,7 @@ hipError_t fwd_general_t(const Problem &p, hipStream_t st)
     const int64_t n = (int64_t)p.B * p.C * p.H * p.W;
     const int maxp = p.H > p.W ? p.H : p.W;
     float *ys = nullptr;
-    hipError_t e = p.ws->take((void **)&ys, (size_t)D * n * sizeof(float));
+    hipError_t e = p.ws->take((void **)&ys, (size_t)general_fwd_bytes(p));
     if (e != hipSuccess || p.ws->counting)
         return e;
     hipLaunchKernelGGL((fwd_general_kernel<S>), dim3((unsigned)(D * p.B * p.C)), dim3(kThreads),
@@ -219,10 +219,8 @@ hipError_t bwd_general_t(const Problem &p, hipStream_t st)
     const int64_t HW = (int64_t)p.H * p.W;
     const int64_t units = (int64_t)D * p.B * p.G;
     const int maxp = p.H > p.W ? p.H : p.W;
-    // dx terms per direction, the groups' fp32 weight gradients, line states
     float *dxs = nullptr;
-    const int64_t nf = D * n + units * 3 * HW + units * HW;
-    hipError_t e = p.ws->take((void **)&dxs, (size_t)nf * sizeof(float));
+    hipError_t e = p.ws->take((void **)&dxs, (size_t)general_bwd_bytes(p));
     if (e != hipSuccess || p.ws->counting)
         return e;
     float *dws = dxs + D * n, *hs = dws + units * 3 * HW;
@@ -245,6 +243,20 @@ hipError_t bwd_general_t(const Problem &p, hipStream_t st)
 }
 
 }  // namespace
+
+// Workspace of the forward: the directions' fp32 terms.
+int64_t general_fwd_bytes(const Problem &p)
+{
+    return (int64_t)__builtin_popcount(p.mask) * p.B * p.C * p.H * p.W * (int64_t)sizeof(float);
+}
+
+// Workspace of the backward: dx terms per direction, the groups' fp32 weight
+// gradients, line states.
+int64_t general_bwd_bytes(const Problem &p)
+{
+    const int64_t HW = (int64_t)p.H * p.W, D = __builtin_popcount(p.mask);
+    return (D * p.B * p.C * HW + D * p.B * p.G * 4 * HW) * (int64_t)sizeof(float);
+}
 
 hipError_t launch_fwd_general(const Problem &p, hipStream_t st)
 {

@@ -1,0 +1,107 @@
+"""The line family (planes with a side of 65 to 256 that no other family takes)
+against the fp64 oracle, at the sizes where it changes its plan: lines of 64,
+65, 128, 129, 256 positions (1, 2 and 4 positions per lane) and 257 (the
+general family), lengths that are no multiple of a lane's positions, lines
+shorter than them, tiles of 32 x 64 pixels with remainders, groups in one and
+several channel chunks, both layouts and types; and gspn_scan_bwd_static, whose
+fixed workspace makes it take smaller rounds or the general family."""
+import numpy as np
+import pytest
+
+import gspn_inputs as gi
+import oracle
+import paper_2606_00746_amd as gspn
+from gpu_util import normwise_err, require_gpu, to_host, tolerance, upload
+from test_parity_gpu import case, check_against_oracle, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    case("line-65x64", 2, 6, 3, 65, 64),
+    case("line-64x65-dirs6", 1, 10, 2, 64, 65, dirs=6),
+    case("line-33x128-cpg9", 1, 9, 1, 33, 128),
+    case("line-129x31-G=C", 2, 3, 3, 129, 31, dirs=13),
+    case("line-127x67-f32", 1, 4, 2, 127, 67, dtype="f32", gate="normal"),
+    case("line-256x254-cpg8", 1, 8, 1, 256, 254, dirs=9),
+    case("line-1x66", 2, 4, 2, 1, 66),
+    case("line-201x1", 1, 4, 2, 201, 1),
+    case("line-3x131-f32-dirs5", 1, 4, 1, 3, 131, dirs=5, dtype="f32", gate="normal"),
+    case("general-257x10", 1, 2, 1, 257, 10),
+]
+
+
+@pytest.mark.parametrize("layout", ["pixel", "blocked"])
+@pytest.mark.parametrize("wl", CASES, ids=lambda w: w.name)
+def test_line_parity(wl, layout):
+    inputs = gi.make_inputs(wl, with_dy=True)
+    got = run_gpu(inputs, wl, True, layout=layout)
+    check_against_oracle(inputs, got, wl, True, f"{wl.name} {layout}")
+
+
+@pytest.mark.parametrize("wl,same", [
+    (case("static-rounds", 4, 24, 6, 100, 101), True),      # rounds of a few groups
+    (case("static-general", 1, 24, 1, 256, 250), False),    # one group does not fit
+], ids=lambda v: getattr(v, "name", ""))
+def test_static_backward_limits(wl, same):
+    """gspn_scan_bwd_static works in 64 MiB: smaller rounds than gspn_scan_bwd
+    give the same bits; where one group's lines do not fit it runs the general
+    family, whose need decides what it refuses."""
+    torch = require_gpu()
+    print(f"[case] {wl.name}", flush=True)
+    inputs = gi.make_inputs(wl, with_dy=True)
+    t = upload(inputs, wl.dtype, wl.dirs)
+    ref = gspn.scan_bwd(t["x"], t["w"], t["lam"], t["u"], t["dy"], wl.dirs)
+    out = [torch.empty_like(v) for v in ref]
+    args = [t[k].data_ptr() for k in ("x", "w", "lam", "u", "dy")] + [v.data_ptr() for v in out]
+    st = gspn.gspn_scan_bwd_static(*args, wl.dirs, wl.B, wl.C, wl.G, wl.H, wl.W, gspn.BF16,
+                                   torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    torch.cuda.synchronize()
+    for k, a, b in zip(("dx", "dw", "dlam", "du"), out, ref):
+        if same:
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16)), k
+        else:
+            assert normwise_err(to_host(a), to_host(b)) <= tolerance(wl.dtype), k
+
+
+def test_caller_with_less_workspace():
+    """A workspace below the query's size but of what the general family takes
+    is accepted: the line family in smaller rounds (the same bits)."""
+    torch = require_gpu()
+    wl = case("less-workspace", 2, 32, 8, 90, 101)
+    print(f"[case] {wl.name}", flush=True)
+    inputs = gi.make_inputs(wl, with_dy=True)
+    t = upload(inputs, wl.dtype, wl.dirs)
+    ref = gspn.scan_bwd(t["x"], t["w"], t["lam"], t["u"], t["dy"], wl.dirs)
+    HW = wl.H * wl.W
+    less = 4 * (4 * wl.B * wl.C * HW + 16 * wl.B * wl.G * HW)
+    st, need = gspn.gspn_workspace_size(gspn.OP_BWD, wl.dirs, wl.B, wl.C, wl.G, wl.H, wl.W,
+                                        gspn.BF16)
+    assert st == 0 and less < need
+    out = [torch.empty_like(v) for v in ref]
+    ws = torch.empty(less, dtype=torch.uint8, device="cuda")
+    ptrs = [t[k].data_ptr() for k in ("x", "w", "lam", "u", "dy")] + [v.data_ptr() for v in out]
+    args = (wl.dirs, wl.B, wl.C, wl.G, wl.H, wl.W, gspn.BF16, ws.data_ptr())
+    stream = torch.cuda.current_stream().cuda_stream
+    assert gspn.gspn_scan_bwd(*ptrs, *args, less - 1, stream) == -9
+    assert gspn.gspn_scan_bwd(*ptrs, *args, less, stream) == 0
+    torch.cuda.synchronize()
+    for k, a, b in zip(("dx", "dw", "dlam", "du"), out, ref):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16)), k
+
+
+def test_line_rounds():
+    """More planes than one round's workspace (512 MB) holds: units of the
+    first, a middle and the last round against the oracle."""
+    wl = case("line-rounds", 3, 192, 12, 130, 129)
+    inputs = gi.make_inputs(wl, with_dy=True)
+    got = run_gpu(inputs, wl, True)
+    cpg = wl.C // wl.G
+    for b, g in [(0, 0), (1, 7), (2, 11)]:
+        sl = oracle.slice_group(inputs, b, g, wl.G)
+        cs = slice(g * cpg, (g + 1) * cpg)
+        part = {"y": got["y"][b:b + 1, cs], "dx": got["dx"][b:b + 1, cs],
+                "dw": got["dw"][:, b:b + 1, g:g + 1], "dlam": got["dlam"][:, b:b + 1, cs],
+                "du": got["du"][:, b:b + 1, cs]}
+        check_against_oracle(sl, part, wl.with_(B=1, C=cpg, G=1), True, f"{wl.name} b={b} g={g}")
+    assert all(np.all(np.isfinite(v)) for v in got.values())
