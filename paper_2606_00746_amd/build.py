@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgspn.so")
 SOURCES = ["api.cpp", "scan_tiny.hip", "scan_small.hip", "scan_med_64.hip", "scan_med_56.hip",
            "scan_med_48.hip", "scan_med_40_32_24.hip", "scan_med.hip", "scan_pm.hip",
-           "scan_wide.hip", "scan_norm.hip", "scan_line.hip", "scan_general.hip", "latent.hip"]
+           "scan_wide.hip", "scan_norm.hip", "scan_plane.hip", "scan_line.hip", "scan_general.hip", "latent.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [

@@ -83,15 +83,21 @@ using namespace gspn;
 
 namespace gspn {
 
-// The kernel family for a problem: the first one that supports its shape.
+// The kernel family for a problem: the fastest one that supports its shape
+// and, where the caller's workspace is limited (p.ws_cap), fits in it.
 hipError_t dispatch_fwd(const Problem &p, hipStream_t s)
 {
     if (med_supported(p))
         return launch_fwd_med(p, s);
     if (tiny_supported(p))
         return launch_fwd_tiny(p, s);
-    if (p.H <= kSmallSide && p.W <= kSmallSide)
-        return launch_fwd_small(p, s);
+    if (p.H <= kSmallSide && p.W <= kSmallSide) {
+        if (small_fwd_preferred(p))
+            return launch_fwd_small(p, s);
+        if (!plane_preferred(p, false) && line_supported(p, false))
+            return launch_fwd_line(p, s);
+        return launch_fwd_plane(p, s);
+    }
     if (wide_supported(p))
         return launch_fwd_wide(p, s);
     if (line_supported(p, false))
@@ -105,8 +111,12 @@ hipError_t dispatch_bwd(const Problem &p, hipStream_t s)
         return launch_bwd_med(p, s);
     if (tiny_supported(p))
         return launch_bwd_tiny(p, s);
-    if (p.H <= kSmallSide && p.W <= kSmallSide)
-        return launch_bwd_small(p, s);
+    if (p.H <= kSmallSide && p.W <= kSmallSide) {
+        const bool plane = p.room(plane_bwd_bytes(p));
+        if (!(plane && plane_preferred(p, true)) && line_supported(p, true))
+            return launch_bwd_line(p, s);
+        return plane ? launch_bwd_plane(p, s) : launch_bwd_small(p, s);
+    }
     if (line_supported(p, true))
         return launch_bwd_line(p, s);
     return launch_bwd_general(p, s);

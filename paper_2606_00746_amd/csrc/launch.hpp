@@ -69,6 +69,11 @@ struct Problem {
     // do with less choose their plan by it, and a call that needs more than
     // this is refused; < 0: the plan the query sizes
     int64_t ws_cap = -1;
+    // whether `bytes` more can be taken under that limit
+    bool room(int64_t bytes) const
+    {
+        return ws_cap < 0 || (((int64_t)ws->used + 255) & ~(int64_t)255) + bytes <= ws_cap;
+    }
 };
 
 // Takes the reserve's parts from p.rs.  Weights the library forms itself
@@ -96,8 +101,15 @@ constexpr int kSmallSide = 64;
 // LDS a workgroup may use on gfx950 (the only target of this library).
 constexpr int kLdsBytes = 160 * 1024;
 
+bool small_fwd_preferred(const Problem &p);
 hipError_t launch_fwd_small(const Problem &p, hipStream_t s);
 hipError_t launch_bwd_small(const Problem &p, hipStream_t s);
+// Planes of any type and layout with both sides up to kSmallSide: whole planes
+// in LDS (scan_plane.hip).
+bool plane_preferred(const Problem &p, bool bwd);
+int64_t plane_bwd_bytes(const Problem &p);
+hipError_t launch_fwd_plane(const Problem &p, hipStream_t s);
+hipError_t launch_bwd_plane(const Problem &p, hipStream_t s);
 bool tiny_supported(const Problem &p);
 hipError_t launch_fwd_tiny(const Problem &p, hipStream_t s);
 hipError_t launch_bwd_tiny(const Problem &p, hipStream_t s);

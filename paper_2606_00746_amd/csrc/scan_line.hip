@@ -879,8 +879,12 @@ constexpr int64_t kRoundBytes = (int64_t)512 << 20;
 constexpr int64_t kSmallBytes = (int64_t)1 << 20;
 constexpr int64_t kPartPad = 64 * 256;           // alignment of a round's parts
 
+// What a call of the general family takes; planes of at most 64 have other
+// fallbacks, which take less.
 int64_t general_bytes(const Problem &p, bool bwd)
 {
+    if (p.H <= kSmallSide && p.W <= kSmallSide)
+        return 0;
     return bwd ? general_bwd_bytes(p) : general_fwd_bytes(p);
 }
 
@@ -931,7 +935,7 @@ LinePlan line_plan(const Problem &p, bool bwd)
     int64_t most = std::max({gen, kRoundBytes, one});
     if (p.ws_cap >= 0)
         most = std::min(most, p.ws_cap - (((int64_t)p.ws->used + 255) & ~(int64_t)255));
-    else if (gen < kSmallBytes)
+    else if (gen > 0 && gen < kSmallBytes)
         most = gen;
     q.fits = one <= most && gen <= most;
     q.ru = std::max<int64_t>(1, std::min(q.units, (most - kPartPad) / q.unit_bytes));

@@ -1,4 +1,7 @@
-// Register-resident line scans for planes with H, W <= 64.
+// Register-resident line scans for planes with H, W <= 64, read from memory
+// step by step: the forward of few planes (small_fwd_preferred), and the
+// backward of callers whose workspace holds neither scan_plane.hip's partial
+// sums nor a round of scan_line.hip.
 //
 // One lane owns one position of a line (the perpendicular axis); a line of P
 // positions occupies T lanes (T = 16, 32 or 64, T >= P) and a wave holds
@@ -391,6 +394,18 @@ int lanes_per_line(int H, int W)
 }
 
 }  // namespace
+
+// The forward of few planes, which is one workgroup's time here as there: no
+// staging, the four directions side by side (us, small / plane / line): 28 x 28
+// bf16, B*C = 256: 17 / 30 / 23 (the call's host time), 1024: 25 / 30 / 32,
+// 12288: 217 / 109 / 258; fp32 1024: 38 / 33 / 30; 37 x 37 bf16 256: 23 / 30 /
+// 24, 1024: 64 / 31 / 42.
+bool small_fwd_preferred(const Problem &p)
+{
+    const int T = lanes_per_line(p.H, p.W);
+    const int64_t wgs = ((int64_t)p.B * p.C * T + 63) / 64;
+    return (p.H <= 40 && p.W <= 40) && wgs * (p.dtype == 0 ? 4 : 2) <= (T == 64 ? 512 : 1024);
+}
 
 hipError_t launch_fwd_small(const Problem &p, hipStream_t st)
 {
