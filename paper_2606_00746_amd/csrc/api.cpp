@@ -98,11 +98,10 @@ hipError_t dispatch_fwd(const Problem &p, hipStream_t s)
             return launch_fwd_line(p, s);
         return launch_fwd_plane(p, s);
     }
-    if (wide_supported(p))
-        return launch_fwd_wide(p, s);
-    if (line_supported(p, false))
+    const bool wide = wide_supported(p);
+    if ((!wide || line_fwd_preferred(p)) && line_supported(p, false))
         return launch_fwd_line(p, s);
-    return launch_fwd_general(p, s);
+    return wide ? launch_fwd_wide(p, s) : launch_fwd_general(p, s);
 }
 
 hipError_t dispatch_bwd(const Problem &p, hipStream_t s)

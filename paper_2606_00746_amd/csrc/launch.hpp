@@ -156,6 +156,7 @@ hipError_t launch_fwd_wide(const Problem &p, hipStream_t s);
 // Planes of any type and layout with both sides up to kLineSide (scan_line.hip).
 constexpr int kLineSide = 256;
 bool line_supported(const Problem &p, bool bwd);
+bool line_fwd_preferred(const Problem &p);
 hipError_t launch_fwd_line(const Problem &p, hipStream_t s);
 hipError_t launch_bwd_line(const Problem &p, hipStream_t s);
 hipError_t launch_fwd_general(const Problem &p, hipStream_t s);

@@ -935,7 +935,7 @@ LinePlan line_plan(const Problem &p, bool bwd)
     int64_t most = std::max({gen, kRoundBytes, one});
     if (p.ws_cap >= 0)
         most = std::min(most, p.ws_cap - (((int64_t)p.ws->used + 255) & ~(int64_t)255));
-    else if (gen > 0 && gen < kSmallBytes)
+    else if (gen > 0 && gen < kSmallBytes && (bwd || !wide_supported(p)))
         most = gen;
     q.fits = one <= most && gen <= most;
     q.ru = std::max<int64_t>(1, std::min(q.units, (most - kPartPad) / q.unit_bytes));
@@ -1157,6 +1157,19 @@ hipError_t line_t(const Problem &p, bool bwd, hipStream_t st)
 bool line_supported(const Problem &p, bool bwd)
 {
     return (p.H > p.W ? p.H : p.W) <= kLineSide && line_plan(p, bwd).fits;
+}
+
+// Pixel-major shapes that the wide family takes too (bf16, sides multiples of
+// 8): with lines of at most 128 positions, or few planes, a wave per direction
+// and plane beats a workgroup per plane (us, wide / line): 128 x 128, B*C =
+// 384: 121 / 91, 2048: 583 / 481; 72 x 72, 2048: 295 / 213; 256 x 256, 8: 96 /
+// 66, 64: 119 / 83; but 256: 240 / 251, 1024: 958 / 1024; 160 x 160, 1024: 407
+// / 491 (4 positions a lane move more bytes than the wide family's rounds).
+bool line_fwd_preferred(const Problem &p)
+{
+    return p.layout == kPixelMajor &&
+           ((p.H <= 128 && p.W <= 128) ||
+            (int64_t)__builtin_popcount(p.mask) * p.B * p.C <= 512);
 }
 
 hipError_t launch_fwd_line(const Problem &p, hipStream_t st)
