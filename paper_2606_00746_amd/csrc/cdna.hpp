@@ -136,6 +136,26 @@ __device__ __forceinline__ void st128(const u32x4 &d, uint32_t voff, uint32_t so
     asm volatile("buffer_store_dwordx4 %0, %1, %2, %3 offen\n\ts_nop 7\n\ts_nop 7"
                  : : "v"(t), "v"(voff), "s"(d), "s"(soff) : "memory");
 }
+// Stores by the compiler with an asm behind them that holds the data registers
+// for the wait states.  For kernels whose scalar registers spill (a descriptor
+// read back from a vector register's lanes needs wait states before a memory
+// instruction takes it, which the compiler inserts for its own stores but not
+// inside an asm block), and for loops with loads in flight (the compiler counts
+// its own stores in its waits for loads; past an asm store each wait would be
+// for that store too).
+__device__ __forceinline__ void st128_held(const u32x4 &d, uint32_t voff, uint32_t soff, uint4 v)
+{
+    const u32x4 t = {v.x, v.y, v.z, v.w};
+    __builtin_amdgcn_raw_buffer_store_b128(t, as_rsrc(d), voff, soff, 0);
+    asm volatile("s_nop 7\n\ts_nop 7" : : "v"(t) : "memory");
+}
+__device__ __forceinline__ void st64_held(const u32x4 &d, uint32_t voff, uint32_t soff, uint32_t a,
+                                          uint32_t b)
+{
+    const u32x2 t = {a, b};
+    __builtin_amdgcn_raw_buffer_store_b64(t, as_rsrc(d), voff, soff, 0);
+    asm volatile("s_nop 7\n\ts_nop 7" : : "v"(t) : "memory");
+}
 // Non-temporal variant for stores whose wave covers whole 128-byte lines
 // (partial-line non-temporal stores are not merged in the L2 and cost more
 // write traffic than they save).

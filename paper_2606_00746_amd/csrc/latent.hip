@@ -629,6 +629,183 @@ __global__ __launch_bounds__(256) void zero_margin_kernel(bf16_t *y, int H, int 
     }
 }
 
+// The parameter product where the planes are whole 8 x 8 blocks of pixels and
+// Cc is a multiple of 32 up to 64 (the latent sublayer's padded grids).  What
+// bounds it is its output, 20 times its input.  A workgroup owns 8 image rows
+// x 16 columns of one image.  The operands are taken the other way around
+// than in the kernels above, pixels as rows and stacked weight rows as
+// columns: a lane then holds one channel and, with the tile's pixels ordered
+// along the pass's blocked layout (8 lines of one position adjacent), half of
+// a 16-byte piece in consecutive registers; one lane swap between the wave's
+// halves makes it a whole piece, so a plane's 8 values go out as one 16-byte
+// store instead of eight of 2 bytes.  64 pixels are whole 128-byte lines of
+// every plane, stored plane by plane: with 32 pixels at a time the half-written
+// lines in flight exceeded the L2 and left it in parts (830 MB written instead
+// of 524, 243 us).  The three taps of a channel are three accumulators of one
+// lane, normalized there (no zero row).  x is staged as [pixel][k], 8-channel
+// chunks of a pixel swizzled by its 8-pixel group, so that a fragment is one
+// 16-byte LDS read.
+// 80 x 80, B = 32, Cc = 64: 202 -> 151 us (524 MB written, 3.5 TB/s).
+// 24 x 24, B = 1 (8 row x 16 column tiles on a few CUs): 45 -> 23 us a call.
+__device__ __forceinline__ int px_word(int j, int chunk)
+{
+    return 32 * j + 4 * (chunk ^ ((j >> 3) & 7));
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void params_blocks_kernel(
+    ProjArgs A)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t xs[kNT * 32];
+
+    const int t = threadIdx.x;
+    const int v = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int l = t & 63, h = l >> 5, l32 = l & 31;
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int b = mdiv(blk, A.div_n);
+    const int nt = blk - b * A.ntiles;
+    const int rb = mdiv(nt, A.div_tw), row0 = 8 * rb, col0 = 16 * (nt - rb * A.tiles_w);
+    const int H = A.H, W = A.W, K = A.K;
+
+    // 2 x 16-byte pieces (8 pixels of channels 2 kp, 2 kp + 1) a thread and round
+    {
+        const rsrc_t xr = make_rsrc(A.x + (int64_t)b * K * A.HW, (uint32_t)(2 * K * A.HW));
+        uint4 p0[2], p1[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int u = t + 256 * i, piece = u & 15, kp = u >> 4;
+            const int c = col0 + 8 * (piece & 1);
+            const uint32_t o = c < W && 2 * kp < K
+                                   ? 2u * (uint32_t)(2 * kp * A.HW + (row0 + (piece >> 1)) * W + c)
+                                   : kDrop;
+            p0[i] = ld128(xr, o, 0);
+            p1[i] = ld128(xr, o, 2u * (uint32_t)A.HW);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int u = t + 256 * i, piece = u & 15, kp = u >> 4;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                xs[px_word(8 * piece + e, kp >> 2) + (kp & 3)] =
+                    __builtin_amdgcn_perm(part(p1[i], e >> 1), part(p0[i], e >> 1),
+                                          (e & 1) ? 0x07060302u : 0x05040100u);
+        }
+    }
+    __syncthreads();
+
+    const int nsteps = (K + 15) >> 4;
+    const int nv = __popc(A.vslots), ncb = A.Cc >> 5;
+    const int nslot = mdiv(A.DCc, A.div_cc);
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+        const bool vert = pass == 0;
+        const int units = (vert ? nv : nslot - nv) * ncb;    // vertical slots come first
+        if (v >= units)
+            continue;
+#pragma unroll 1
+        for (int un = v; un < units; un += 4) {
+            const int sl = un / ncb + (vert ? 0 : nv), c0 = 32 * (un % ncb);
+            const int64_t wr = (int64_t)sl * A.Cc + c0 + l32;    // this lane's channel
+            auto weights = [&](const bf16_t *src, bf16x8_t (&f)[kKS / 16]) {
+#pragma unroll
+                for (int s = 0; s < kKS / 16; ++s) {
+                    const int k = 16 * s + 8 * h;
+                    if (s < nsteps)
+                        f[s] = k < K ? *reinterpret_cast<const bf16x8_t *>(src + k) : bf16x8_t{};
+                }
+            };
+            bf16x8_t f[5][kKS / 16];
+            weights(A.lu + wr * K, f[0]);
+            weights(A.ll + wr * K, f[1]);
+#pragma unroll
+            for (int m = 0; m < 3; ++m)
+                weights(A.lw + (wr * 3 + m) * K, f[2 + m]);
+            const int64_t plane0 = ((int64_t)sl * A.B + b) * A.Cc + c0;
+            const uint32_t pb = 2u * (uint32_t)A.HW;         // bytes of a plane
+            const u32x4 du = make_sdesc(A.u + plane0 * A.HW, 32u * pb);
+            const u32x4 dl = make_sdesc(A.lam + plane0 * A.HW, 32u * pb);
+            const u32x4 dw = make_sdesc(A.w + plane0 * 3 * A.HW, 96u * pb);
+            const uint32_t vo = (uint32_t)l32 * pb + 16u * h, vw = (uint32_t)l32 * 3u * pb + 16u * h;
+
+            // 64 pixels, 8 positions of 8 lines: a plane's 128 contiguous bytes.
+            // Vertical: 8 columns of the 8 rows; horizontal: 8 rows of 8 columns.
+#pragma unroll 1
+            for (int pr = 0; pr < 2; ++pr) {
+                if (col0 + 8 * pr >= W)      // a tile may reach past the plane
+                    break;
+                bf16x8_t px[2][kKS / 16];
+#pragma unroll
+                for (int ct = 0; ct < 2; ++ct) {
+                    const int g = 4 * ct + (l32 >> 3), e = l32 & 7;
+                    const int js = (vert ? 16 * e + g : 16 * g + e) + 8 * pr;
+#pragma unroll
+                    for (int s = 0; s < kKS / 16; ++s)
+                        if (s < nsteps)
+                            px[ct][s] = *reinterpret_cast<const bf16x8_t *>(&xs[px_word(js, 2 * s + h)]);
+                }
+                auto product = [&](int m, int ct) {
+                    f32x16_t acc;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        acc[r] = 0.f;
+#pragma unroll
+                    for (int s = 0; s < kKS / 16; ++s)
+                        if (s < nsteps)
+                            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(px[ct][s], f[m][s], acc, 0,
+                                                                          0, 0);
+                    return acc;
+                };
+                const int p0 = vert ? col0 + 8 * pr : row0;
+                const uint32_t so =
+                    16u * (uint32_t)(vert ? W * rb + p0 : H * (col0 / 8 + pr) + p0);
+                // positions 2 q, 2 q + 1 of the lane's channel, packed: the lower half
+                // of the wave stores the first, the upper one the second
+                auto store = [&](const u32x4 &d, uint32_t voff, uint32_t soff,
+                                 const uint32_t (&o)[4][4]) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const auto s0 = __builtin_amdgcn_permlane32_swap(o[q][0], o[q][2], false, false);
+                        const auto s1 = __builtin_amdgcn_permlane32_swap(o[q][1], o[q][3], false, false);
+                        st128_held(d, voff, soff + 32u * (uint32_t)q,
+                                   make_uint4(s0[0], s1[0], s0[1], s1[1]));
+                    }
+                };
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const f32x16_t a[2] = {product(m, 0), product(m, 1)};
+                    uint32_t o[4][4];
+#pragma unroll
+                    for (int r = 0; r < 32; r += 2)
+                        o[r >> 3][(r >> 1) & 3] = pack2(a[r >> 4][r & 15], a[r >> 4][(r & 15) + 1]);
+                    store(m ? dl : du, vo, so, o);
+                }
+                uint32_t o[3][4][4];
+#pragma unroll
+                for (int ct = 0; ct < 2; ++ct) {
+                    const f32x16_t a[3] = {product(2, ct), product(3, ct), product(4, ct)};
+                    const int P = vert ? A.Wv : A.Hv;
+#pragma unroll
+                    for (int r = 0; r < 16; r += 2) {
+                        // the position is uniform, the lines are the registers
+                        const int p = p0 + 4 * ct + (r >> 2);
+                        float w[2][3];
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            const float t3[3] = {a[0][r + e], a[1][r + e], a[2][r + e]};
+                            norm3(t3, p > 0, p < P - 1, w[e]);
+                        }
+#pragma unroll
+                        for (int m = 0; m < 3; ++m)
+                            o[m][2 * ct + (r >> 3)][(r >> 1) & 3] = pack2(w[0][m], w[1][m]);
+                    }
+                }
+#pragma unroll
+                for (int m = 0; m < 3; ++m)
+                    store(dw, vw, so + (uint32_t)m * pb, o[m]);
+            }
+        }
+    }
+}
+
 template <Mode MODE>
 hipError_t launch_proj(ProjArgs &A, hipStream_t st)
 {
@@ -702,6 +879,15 @@ hipError_t launch_latent_params(const void *xc, const void *lu, const void *ll, 
     A.ntiles = ((H + 7) / 8) * A.tiles_w;
     A.div_cc = make_magic((uint32_t)Cc);
     A.div_tw = make_magic((uint32_t)A.tiles_w);
+    // whole 8 x 8 blocks: faster at every size measured (B = 1, 24 x 24 to B = 32,
+    // 80 x 80; Cc = 32 and 64: 1.1 to 2 times); other sides keep the tiles below,
+    // whose stores are 2 bytes at any alignment
+    if (Cc % 32 == 0 && Cc <= kKS && H % 8 == 0 && W % 8 == 0) {
+        A.div_n = make_magic((uint32_t)A.ntiles);
+        hipLaunchKernelGGL(params_blocks_kernel, dim3((unsigned)((int64_t)B * A.ntiles)), dim3(256),
+                           0, st, A);
+        return hipGetLastError();
+    }
     return launch_proj<Mode::Params>(A, st);
 }
 

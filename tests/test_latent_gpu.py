@@ -93,6 +93,20 @@ def test_latent_params_match_oracle(lw):
     assert np.all(got_w[ref["w"] == 0.0] == 0.0), f"{lw.name} off-grid taps not 0"
 
 
+# whole 8 x 8 blocks with Cc of 32 and 64: one row of blocks and one column of
+# them, tiles that reach past the plane (W of an odd number of 8-column
+# blocks), direction subsets with vertical or horizontal passes only
+@pytest.mark.parametrize("lw", [
+    _lw("blocks-8x8", 3, 16, 32, 8, 8),
+    _lw("blocks-8x40-dirs6", 2, 16, 64, 8, 40, dirs=6),
+    _lw("blocks-40x8-dirs3", 2, 16, 32, 40, 8, dirs=3),
+    _lw("blocks-24x16-dirs12", 1, 16, 64, 24, 16, dirs=12),
+    _lw("blocks-72x56", 9, 16, 64, 72, 56),
+], ids=lambda w: w.name)
+def test_latent_params_whole_blocks(lw):
+    test_latent_params_match_oracle(lw)
+
+
 # sides that are not multiples of 8 run the latent scan on a grid padded to
 # whole 8-line blocks: scans that start in the padding (B2T, R2L), wide
 # padded grids, square and oblong ones
