@@ -91,6 +91,8 @@ hipError_t dispatch_fwd(const Problem &p, hipStream_t s)
         return launch_fwd_med(p, s);
     if (tiny_supported(p))
         return launch_fwd_tiny(p, s);
+    if (wide_sum_supported(p))
+        return launch_fwd_wide_sum(p, s);
     if (p.H <= kSmallSide && p.W <= kSmallSide) {
         if (small_fwd_preferred(p))
             return launch_fwd_small(p, s);

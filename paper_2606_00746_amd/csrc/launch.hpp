@@ -126,6 +126,7 @@ hipError_t med_fwd(const Problem &p, hipStream_t s);
 template <int S>
 hipError_t med_bwd(const Problem &p, hipStream_t s);
 bool wide_supported(const Problem &p);
+bool wide_sum_supported(const Problem &p);
 // Pixel-major problems of the register-streamed shapes: the weights are
 // re-laid out into the blocked order (launch_w_to_blocked, workspace of
 // |w| bytes) when a group has at least kReblockCpg channels, so that the
@@ -153,6 +154,7 @@ hipError_t launch_fwd_pm(const Problem &p, hipStream_t s);
 // launch_norm and the re-layout of launch_w_to_blocked in one pass.
 hipError_t launch_norm_blocked(const Problem &p, const void *wt, void *wb, hipStream_t s);
 hipError_t launch_fwd_wide(const Problem &p, hipStream_t s);
+hipError_t launch_fwd_wide_sum(const Problem &p, hipStream_t s);
 // Planes of any type and layout with both sides up to kLineSide (scan_line.hip).
 constexpr int kLineSide = 256;
 bool line_supported(const Problem &p, bool bwd);

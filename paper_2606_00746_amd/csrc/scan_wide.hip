@@ -12,8 +12,10 @@
 //    rotates;
 //  * lam, u and w come in 8-line blocks of 16-byte coalesced loads, one
 //    block ahead of use.
-// A 256 x 256 fp32 merge plane does not fit in LDS, so each direction writes
-// u_d * h_d to an fp32 plane in its own line-major order (whole lines per
+// Where the plane's fp32 sum fits in LDS beside x (sides up to about 160, blocked
+// tensors), the directions add to it there (fwd_wide_sum_kernel; this also takes
+// sides below 65 that no square family has).  A 256 x 256 sum does not fit, so
+// there each direction writes u_d * h_d to an fp32 plane in its own line-major order (whole lines per
 // store) and a tiled kernel sums the directions in direction-bit order,
 // transposing the horizontal ones through LDS, and stores y once.  The scan
 // and the sum alternate in rounds of planes, so that the sum finds much of
@@ -92,8 +94,63 @@ __device__ __forceinline__ void neighbours(const float (&h)[NPL], float (&left)[
 //   kStore  the recurrence, u * h written to the direction's fp32 plane;
 //   kEnd    the recurrence, nothing written: the caller keeps the end state;
 //   kHomog  the recurrence without the injection lam * x (only w is read):
-//           it carries a state across the blocks, h -> Phi h.
-enum PassMode { kStore, kEnd, kHomog };
+//           it carries a state across the blocks, h -> Phi h;
+//   kSum    the recurrence, u * h added to the plane's fp32 sum in LDS.
+enum PassMode { kStore, kEnd, kHomog, kSum };
+
+// The turns that the four direction waves take at the sum in LDS.  After
+// every block of 8 lines the vertical waves add theirs, then the horizontal
+// ones; two opposite scans meet on the same lines in the middle block of an
+// odd count, where the reverse one adds after the forward one.  So no two
+// waves ever touch a pixel in the same turn (plain reads and writes), and the
+// order of the additions is the same in every run.  A turn ends with a
+// barrier that every wave passes, also one that has no direction or whose
+// scan is the shorter one; a vertical wave takes the horizontal turn's end
+// with it into its next block, and computes meanwhile.
+struct Turns {
+    int nv, nh;    // blocks of 8 lines of the vertical and horizontal scans
+    __device__ __forceinline__ int ticks() const { return nv > nh ? nv : nh; }
+    static __device__ __forceinline__ bool middle(int n, int t) { return (n & 1) && t == (n >> 1); }
+    template <bool REV, typename F>
+    __device__ __forceinline__ void turn(int n, int t, bool mine, F add) const
+    {
+        const bool mid = middle(n, t);
+        if (REV && mid)
+            lds_barrier();
+        if (mine)
+            add();
+        if (!REV && mid)
+            lds_barrier();
+        lds_barrier();
+    }
+    // block t of a wave's scan, add() the wave's additions (mine: it has any)
+    template <bool VERT, bool REV, typename F>
+    __device__ __forceinline__ void block(int t, bool mine, F add) const
+    {
+        if (VERT) {
+            if (t > 0)
+                turn<false>(nh, t - 1, false, [] {});
+            turn<REV>(nv, t, mine, add);
+        } else {
+            turn<false>(nv, t, false, [] {});
+            turn<REV>(nh, t, mine, add);
+        }
+    }
+    // the blocks from t on, of a wave with nothing more to add
+    template <bool VERT>
+    __device__ __forceinline__ void rest(int t) const
+    {
+#pragma unroll 1
+        for (; t < ticks(); ++t)
+            block<VERT, false>(t, false, [] {});
+        if (VERT)
+            turn<false>(nh, ticks() - 1, false, [] {});
+    }
+};
+
+// The fp32 sum of a plane in LDS: an odd number of dwords per row, so that row
+// and column walks are both free of bank conflicts.
+__host__ __device__ inline int sum_pitch(int W) { return W | 1; }
 
 // One direction of one channel plane over the scan's line blocks fb0 .. fb1-1
 // (blocks of 8 lines in scan order), starting from state h (0 before the
@@ -105,7 +162,7 @@ enum PassMode { kStore, kEnd, kHomog };
 template <int NPL, bool VERT, bool REV, int HC, int WC, int MODE>
 __device__ __forceinline__ void wide_dir(int lane, int H_, int W_, rsrc_t lam, rsrc_t u, rsrc_t w,
                                          const uint8_t *xs, u32x4 ys, int fb0, int fb1,
-                                         float (&h)[NPL])
+                                         float (&h)[NPL], float *sum = nullptr)
 {
     const int H = HC ? HC : H_, W = WC ? WC : W_;
     const int L = VERT ? H : W, P = VERT ? W : H;
@@ -128,7 +185,7 @@ __device__ __forceinline__ void wide_dir(int lane, int H_, int W_, rsrc_t lam, r
         for (int m = 0; m < NPL; ++m) {
             if (MODE != kHomog)
                 pc.l[m] = ld_piece<false, VERT, true>(lam, jc[m], sq, P, W);
-            if (MODE == kStore)
+            if (MODE == kStore || MODE == kSum)
                 pc.u[m] = ld_piece<false, VERT, true>(u, jc[m], sq, P, W);
             pc.w0[m] = ld_piece<false, VERT, false>(w, jc[m], sq, P, W);
             pc.w1[m] = ld_piece<false, VERT, false>(w, jc[m], sq, P, W, wplane);
@@ -145,6 +202,7 @@ __device__ __forceinline__ void wide_dir(int lane, int H_, int W_, rsrc_t lam, r
         for (int m = 0; m < NPL; ++m)
             xb[m] = VERT ? 4u * (uint32_t)(l0 * pdw) + 2u * (uint32_t)jc[m]
                          : 4u * (uint32_t)(jc[m] * pdw) + 2u * (uint32_t)l0;
+        float v[NPL][8];                                // kSum: u * h of the block
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const int i = 8 * fb + t;
@@ -176,6 +234,36 @@ __device__ __forceinline__ void wide_dir(int lane, int H_, int W_, rsrc_t lam, r
                                 __float_as_uint(elem(pc.u[m], e) * h[m]));
                 }
             }
+            if (MODE == kSum) {
+#pragma unroll
+                for (int m = 0; m < NPL; ++m)
+                    v[m][e] = elem(pc.u[m], e) * h[m];
+                if (!HC && NPL <= 2)
+                    step_fence();     // keeps the registers at 3 waves per SIMD
+            }
+        }
+        if (MODE == kSum) {
+            step_fence();
+            const Turns turns{H / 8, W / 8};
+            turns.block<VERT, REV>(fb, true, [&] {
+                int ap = sum_pitch(W);
+                asm("" : "+s"(ap));
+#pragma unroll
+                for (int m = 0; m < NPL; ++m) {
+                    int jm = jc[m];
+                    asm("" : "+v"(jm));
+                    float *a = sum + (VERT ? l0 * ap + jm : jm * ap + l0);
+                    const int st = VERT ? ap : 1;
+                    if (valid[m]) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            v[m][e] += a[e * st];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            a[e * st] = v[m][e];
+                    }
+                }
+            });
         }
         step_fence();
     };
@@ -310,16 +398,16 @@ __device__ __forceinline__ void wide_vert_pm(int lane, int H_, int W_, rsrc_t la
 template <int NPL, int HC, int WC, int MODE>
 __device__ __forceinline__ void wide_pass(int d, int lane, int H, int W, rsrc_t rl, rsrc_t ru,
                                           rsrc_t rw, const uint8_t *xs, u32x4 yd, int fb0,
-                                          int fb1, float (&h)[NPL])
+                                          int fb1, float (&h)[NPL], float *sum = nullptr)
 {
     if (d == 0)
-        wide_dir<NPL, true, false, HC, WC, MODE>(lane, H, W, rl, ru, rw, xs, yd, fb0, fb1, h);
+        wide_dir<NPL, true, false, HC, WC, MODE>(lane, H, W, rl, ru, rw, xs, yd, fb0, fb1, h, sum);
     else if (d == 1)
-        wide_dir<NPL, true, true, HC, WC, MODE>(lane, H, W, rl, ru, rw, xs, yd, fb0, fb1, h);
+        wide_dir<NPL, true, true, HC, WC, MODE>(lane, H, W, rl, ru, rw, xs, yd, fb0, fb1, h, sum);
     else if (d == 2)
-        wide_dir<NPL, false, false, HC, WC, MODE>(lane, H, W, rl, ru, rw, xs, yd, fb0, fb1, h);
+        wide_dir<NPL, false, false, HC, WC, MODE>(lane, H, W, rl, ru, rw, xs, yd, fb0, fb1, h, sum);
     else
-        wide_dir<NPL, false, true, HC, WC, MODE>(lane, H, W, rl, ru, rw, xs, yd, fb0, fb1, h);
+        wide_dir<NPL, false, true, HC, WC, MODE>(lane, H, W, rl, ru, rw, xs, yd, fb0, fb1, h, sum);
 }
 
 // x plane of channel plane pc -> LDS: coalesced 16-byte pieces into padded rows.
@@ -395,6 +483,69 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             const int NB = (d < 2 ? H : W) / 8;
             wide_pass<NPL, HC, WC, kStore>(d, lane, H, W, rl, ru, rw, xs, yd, 0, NB, h);
         }
+    }
+}
+
+// Blocked planes whose fp32 sum fits in LDS beside x: the direction waves add
+// u * h to it there (Turns) and y goes out once, instead of D fp32 planes
+// written and read back by a launch of their own (6 bytes of LDS a pixel
+// against 8 D bytes of memory traffic).  Bound by memory where a CU holds two
+// or more workgroups: 80 x 80, B*C = 2048, per-channel taps: 252 -> 122 us (577
+// MB, 4.7 TB/s); with one workgroup (sides from about 116) by the steps' latency,
+// so there the loop is left to the compiler's schedule (128 x 128, B*C = 1024:
+// 167 us with a fence per step, 158 without).
+template <int NPL, int HC, int WC>
+__global__ __launch_bounds__(256, !HC && NPL <= 2 ? 3 : 1) void fwd_wide_sum_kernel(
+    const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const bf16_t *__restrict__ lam,
+    const bf16_t *__restrict__ u, bf16_t *__restrict__ y, int mask, int B, int C, int G, int H_,
+    int W_, Magic divC, Magic divCpg, Magic divNq, Magic divW2)
+{
+    const int H = HC ? HC : H_, W = WC ? WC : W_;
+    extern __shared__ uint32_t xs32[];
+    const uint8_t *xs = reinterpret_cast<const uint8_t *>(xs32);
+    float *sum = reinterpret_cast<float *>(xs32 + H * wide_pitch_dw(W));
+    const int d = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
+    const int lane = threadIdx.x & 63;
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int b = mdiv(blk, divC);
+    const int c = blk - b * C;
+    const int g = mdiv(c, divCpg);
+    const int64_t HW = (int64_t)H * W;
+    const int64_t pc = ((int64_t)b * C + c) * HW;
+    const int ap = sum_pitch(W);
+
+    stage_x_plane<WC>(x, pc, H, W, divNq, xs32);
+    for (int t = threadIdx.x; t < H * ap; t += 256)
+        sum[t] = 0.f;
+    lds_barrier();
+
+    const Turns turns{H / 8, W / 8};
+    if ((mask >> d) & 1) {
+        const int s = __popc(mask & ((1 << d) - 1));
+        const int64_t pd = (((int64_t)s * B + b) * C + c) * HW;
+        const int64_t pw = (((int64_t)s * B + b) * G + g) * 3 * HW;
+        const rsrc_t rl = make_rsrc(lam + pd, (uint32_t)(2 * HW));
+        const rsrc_t ru = make_rsrc(u + pd, (uint32_t)(2 * HW));
+        const rsrc_t rw = make_rsrc(w + pw, (uint32_t)(6 * HW));
+        float h[NPL];
+#pragma unroll
+        for (int m = 0; m < NPL; ++m)
+            h[m] = 0.f;
+        wide_pass<NPL, HC, WC, kSum>(d, lane, H, W, rl, ru, rw, xs, u32x4{}, 0, (d < 2 ? H : W) / 8,
+                                   h, sum);
+        if (d < 2)
+            turns.rest<true>(H / 8);
+        else
+            turns.rest<false>(W / 8);
+    } else {
+        turns.rest<false>(0);
+    }
+    // the last turn's barrier is behind every wave
+    const u32x4 yd = make_sdesc(y + pc, (uint32_t)(2 * HW));
+    for (int t = threadIdx.x; t < (int)HW / 2; t += 256) {
+        const int r = WC ? t / (WC / 2) : mdiv(t, divW2), q = t - r * (W / 2);
+        const float *a = sum + r * ap + 2 * q;
+        st32(yd, 4u * (uint32_t)t, 0, pack2(a[0], a[1]));
     }
 }
 
@@ -599,6 +750,24 @@ __global__ __launch_bounds__(256) void sum_wide_kernel(const float *__restrict__
     }
 }
 
+size_t wide_sum_lds(int H, int W) { return (size_t)4 * H * (wide_pitch_dw(W) + sum_pitch(W)); }
+
+template <int NPL, int HC, int WC>
+hipError_t fwd_wide_sum_t(const Problem &p, hipStream_t st)
+{
+    const size_t lds = wide_sum_lds(p.H, p.W);
+    const hipError_t e = hipFuncSetAttribute((const void *)fwd_wide_sum_kernel<NPL, HC, WC>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL((fwd_wide_sum_kernel<NPL, HC, WC>), dim3((unsigned)(p.B * p.C)), dim3(256), lds, st,
+                       (const bf16_t *)p.x, (const bf16_t *)p.w, (const bf16_t *)p.lam,
+                       (const bf16_t *)p.u, (bf16_t *)p.y, p.mask, p.B, p.C, p.G, p.H, p.W,
+                       make_magic((uint32_t)p.C), make_magic((uint32_t)(p.C / p.G)),
+                       make_magic((uint32_t)(p.W / 8)), make_magic((uint32_t)(p.W / 2)));
+    return hipGetLastError();
+}
+
 // v: with the vertical directions read in place, the call's pixel-major
 // tensors (p then holds the horizontal directions' blocked copies).
 template <int NPL, int HC, int WC, bool VPM>
@@ -790,16 +959,10 @@ hipError_t fwd_wide_l(const Problem &p, hipStream_t st, float *ys, float *states
 {
     const int side = p.H > p.W ? p.H : p.W;
     const int npl = (side + 63) / 64;
-    // the square planes of 256 and 128 get kernels with their shape built in
-    if (K > 1) {
-        if (p.H == 256 && p.W == 256)
-            return fwd_wide_chunked_t<4, 256, 256>(p, st, ys, states, lds, K);
-        if (p.H == 128 && p.W == 128)
-            return fwd_wide_chunked_t<2, 128, 128>(p, st, ys, states, lds, K);
-        return npl <= 2 ? fwd_wide_chunked_t<2, 0, 0>(p, st, ys, states, lds, K)
-               : npl == 3 ? fwd_wide_chunked_t<3, 0, 0>(p, st, ys, states, lds, K)
-                          : fwd_wide_chunked_t<4, 0, 0>(p, st, ys, states, lds, K);
-    }
+    // the square planes of 256 get kernels with their shape built in; they are also
+    // the only ones long enough both ways for chunks (wide_chunks)
+    if (K > 1)
+        return fwd_wide_chunked_t<4, 256, 256>(p, st, ys, states, lds, K);
     const int p0 = plane0, n = nplanes;
     if (v != nullptr) {
         if (p.H == 256 && p.W == 256)
@@ -810,11 +973,9 @@ hipError_t fwd_wide_l(const Problem &p, hipStream_t st, float *ys, float *states
     }
     if (p.H == 256 && p.W == 256)
         return fwd_wide_t<4, 256, 256, false>(p, st, ys, lds, p0, n, nullptr);
-    if (p.H == 128 && p.W == 128)
-        return fwd_wide_t<2, 128, 128, false>(p, st, ys, lds, p0, n, nullptr);
-    return npl <= 2 ? fwd_wide_t<2, 0, 0, false>(p, st, ys, lds, p0, n, nullptr)
-           : npl == 3 ? fwd_wide_t<3, 0, 0, false>(p, st, ys, lds, p0, n, nullptr)
-                      : fwd_wide_t<4, 0, 0, false>(p, st, ys, lds, p0, n, nullptr);
+    // blocked planes up to 128 a side sum in LDS (wide_sum_supported)
+    return npl <= 3 ? fwd_wide_t<3, 0, 0, false>(p, st, ys, lds, p0, n, nullptr)
+                    : fwd_wide_t<4, 0, 0, false>(p, st, ys, lds, p0, n, nullptr);
 }
 
 // Planes per round of the single-pass forward.  Each round's direction sum
@@ -852,6 +1013,34 @@ bool wide_supported(const Problem &p)
     if (side > 64 * kMaxNpl)
         return false;
     return wide_lds_bytes(p.H, p.W) <= (size_t)kLdsBytes;
+}
+
+// Blocked bf16 planes with whole 8-line blocks whose fp32 sum fits in LDS: sides
+// up to about 160.  Against the D fp32 planes and their sum (us, before / now):
+// 80 x 80, B*C = 2048: 252 / 122, 776: 102 / 48, 32: 29 / 23; 72 x 72, 2048: 199 /
+// 76; 112 x 112, 1024: 208 / 117; 128 x 128, 1024: 241 / 158, 264: 64 / 63, 32: 32 /
+// 32; 152 x 144, 512: 145 / 112; 256 x 80, 1024: 416 / 370.  Against the families of
+// sides up to 64, which turn blocked planes around: 40 x 56, 6144 in 192 groups:
+// 595 / 66, 32 x 24, 2048: 90 / 19, 16 x 24, 6144: 52 / 26, 40 x 24, 32: 22 / 13.  The
+// squares that have a family of their own were measured too and keep it: 64 x 64,
+// 6144: 103 / 107, 24 x 24: 29 / 31, 16 x 16: 19 / 21, 56 x 56: 93 / 90.
+bool wide_sum_supported(const Problem &p)
+{
+    return p.layout != kPixelMajor && wide_supported(p) &&
+           wide_sum_lds(p.H, p.W) <= (size_t)kLdsBytes;
+}
+
+hipError_t launch_fwd_wide_sum(const Problem &p, hipStream_t st)
+{
+    if (p.ws->counting)
+        return hipSuccess;
+    if (p.H == 128 && p.W == 128)
+        return fwd_wide_sum_t<2, 128, 128>(p, st);
+    const int side = std::max(p.H, p.W);
+    return side <= 64    ? fwd_wide_sum_t<1, 0, 0>(p, st)
+           : side <= 128 ? fwd_wide_sum_t<2, 0, 0>(p, st)
+           : side <= 192 ? fwd_wide_sum_t<3, 0, 0>(p, st)
+                         : fwd_wide_sum_t<4, 0, 0>(p, st);
 }
 
 hipError_t launch_fwd_wide(const Problem &p, hipStream_t st)
