@@ -1,4 +1,5 @@
-// Line scans for planes with a side above 64 (up to GSPN_MAX_SIDE).
+// Line scans for planes with a side above 256 (up to GSPN_MAX_SIDE), and for
+// callers whose workspace holds no round of scan_line.hip.
 //
 // A workgroup runs one line scan; each thread owns positions j, j + NT, ...
 // of the line and the previous line's states are read from a triple-buffered
