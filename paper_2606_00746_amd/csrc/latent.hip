@@ -93,6 +93,21 @@ __device__ __forceinline__ void bst16(rsrc_t r, uint32_t voff, uint32_t soff, ui
     __builtin_amdgcn_raw_buffer_store_b16(v, r, voff, soff, 0);
 }
 
+// Stores of PX (2 or 4) adjacent pixels, by the compiler as well; the wider one
+// with an asm behind it that holds its registers for the wait states.
+template <int PX>
+__device__ __forceinline__ void bst_pixels(rsrc_t r, uint32_t voff, uint32_t soff, uint32_t lo,
+                                           uint32_t hi)
+{
+    if (PX == 2) {
+        __builtin_amdgcn_raw_buffer_store_b32(lo, r, voff, soff, 0);
+    } else {
+        const u32x2 t = {lo, hi};
+        __builtin_amdgcn_raw_buffer_store_b64(t, r, voff, soff, 0);
+        asm volatile("s_nop 7\n\ts_nop 7" : : "v"(t) : "memory");
+    }
+}
+
 // A byte offset beyond the range of every store descriptor of these kernels
 // (each covers one image's maps or less, which the entry points keep under
 // 2 GiB): the buffer's range check discards the store.  Stores of padding
@@ -246,7 +261,15 @@ __device__ __forceinline__ bf16x8_t b_fragment(const uint16_t *xs, int s, int h,
     return bf;
 }
 
-template <Mode MODE>
+// PX: adjacent pixels of a row that a lane stores at once (plain product; 1
+// for the parameters).  Lane column l32 of accumulators PX q .. PX q + PX - 1
+// are then pixels 32 PX q + PX l32 .. + PX - 1 of the tile, so that a store
+// writes 64 PX contiguous bytes a row with one conversion per two values and
+// one scalar offset per PX.  What bounds the kernel is that work around the
+// stores; the results are the same bits for every PX.  P_up (M = 1152, K = 64,
+// B = 32) at 74 x 74, PX 1 -> 4: 142 -> 122 us (3.7 TB/s); at 73 x 74, PX
+// 1 -> 2: 142 -> 138; 768 x 16 at 56 x 56, B = 4, PX 1 -> 4: 13.4 -> 12.2.
+template <Mode MODE, int PX>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void proj_rows_kernel(
     ProjArgs A)
 {
@@ -292,7 +315,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     uint32_t po[4];
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
-        const int jp = 32 * ct + l32;
+        const int jp = 32 * PX * (ct / PX) + PX * l32 + ct % PX;
         int js = jp;                      // the pixel's column in the staged block
         if (fast) {
             const int rl = pass == 0 ? (jp & 7) : ((jp >> 3) & 7);
@@ -372,9 +395,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
         if (rn < RT)
             load_a(rn, an);
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
+        for (int ct = 0; ct < 4; ct += PX) {
             const bool pv = ppix[ct] >= 0;     // a pixel of the image (not padding)
-            if (MODE == Mode::Plain) {
+            if (PX > 1) {
+                // the PX pixels are all of the image or all beyond it, since
+                // PX divides the image's pixels
+                const uint32_t vo = 2u * (uint32_t)(ppix[ct] + 4 * h * A.HW);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int m = 32 * rt + 8 * (r >> 2) + (r & 3);
+                    bst_pixels<PX>(yd, pv && m + 4 * h < A.M ? vo : kDrop,
+                                   2u * (uint32_t)(m * A.HW), pack2(acc[ct][r], acc[(ct + 1) & 3][r]),
+                                   PX == 4 ? pack2(acc[(ct + 2) & 3][r], acc[(ct + 3) & 3][r]) : 0u);
+                }
+            } else if (MODE == Mode::Plain) {
                 // the lane's part of the offset in a register, the row's in soffset
                 const uint32_t vo = 2u * (uint32_t)(ppix[ct] + 4 * h * A.HW);
 #pragma unroll
@@ -812,7 +846,18 @@ hipError_t launch_proj(ProjArgs &A, hipStream_t st)
     if (A.K <= kKS) {
         A.div_n = make_magic((uint32_t)A.ntiles);
         const int64_t nblk = (int64_t)A.B * A.ntiles;
-        hipLaunchKernelGGL(proj_rows_kernel<MODE>, dim3((unsigned)nblk), dim3(256), 0, st, A);
+        // as many pixels a store as keep it aligned in every row of y (whose
+        // base is 16-byte aligned); more were faster wherever they fit (the
+        // times stand at the kernel)
+        if (MODE == Mode::Plain && A.HW % 4 == 0)
+            hipLaunchKernelGGL((proj_rows_kernel<Mode::Plain, 4>), dim3((unsigned)nblk), dim3(256),
+                               0, st, A);
+        else if (MODE == Mode::Plain && A.HW % 2 == 0)
+            hipLaunchKernelGGL((proj_rows_kernel<Mode::Plain, 2>), dim3((unsigned)nblk), dim3(256),
+                               0, st, A);
+        else
+            hipLaunchKernelGGL((proj_rows_kernel<MODE, 1>), dim3((unsigned)nblk), dim3(256), 0, st,
+                               A);
     } else {
         if (MODE == Mode::Plain) {
             // the stage kernel tiles the input pixels; output pixels with no

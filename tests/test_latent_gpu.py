@@ -62,6 +62,23 @@ def test_project_matches_oracle(B, M, K, H, W):
     _close_bf16(y, oracle.project(a, x), f"project {B}x{M}x{K} {H}x{W}")
 
 
+# K <= 64: stores of 4, 2 and 1 pixels (H * W a multiple of 4, of 2, odd), one
+# pixel group alone, tiles that end inside and at a group, rows of a part tile
+@pytest.mark.parametrize("B,M,K,H,W", [
+    (1, 1, 8, 1, 4), (1, 33, 64, 1, 2), (2, 35, 16, 6, 22), (3, 100, 64, 10, 13),
+    (2, 129, 40, 8, 16), (2, 61, 64, 13, 10), (2, 37, 24, 11, 11),
+])
+def test_project_pixels_per_store(B, M, K, H, W):
+    test_project_matches_oracle(B, M, K, H, W)
+
+
+# P_up from a padded grid: 10 x 13 (pairs of pixels across the padded rows'
+# ends), 10 x 14 (groups of 4 that span two rows)
+@pytest.mark.parametrize("H,W", [(10, 13), (10, 14), (74, 74)])
+def test_latent_fwd_pixels_per_store(H, W):
+    test_latent_fwd_matches_oracle(_lw(f"store-{H}x{W}", 2, 48, 32, H, W))
+
+
 LATENT_CASES = [
     _lw("tiny-5x7", 1, 16, 8, 5, 7),
     _lw("vit-37x37", 2, 64, 16, 37, 37),
