@@ -43,28 +43,13 @@
 #include "cdna.hpp"
 #include "device.hpp"
 #include "launch.hpp"
+#include "plane_lds.hpp"
 
 namespace gspn {
 
 namespace {
 
 using namespace cdna;
-
-// dwords of a pixel's record and of a tap entry
-template <typename S>
-struct Rec;
-template <>
-struct Rec<bf16_t> {
-    static constexpr int N = 3;     // x | dy, u | lam, sum
-    static constexpr int WN = 2;    // w0 | w1, w2
-    static constexpr int E = 2;     // elements of a dword
-};
-template <>
-struct Rec<float> {
-    static constexpr int N = 5;     // x, dy, u, lam, sum
-    static constexpr int WN = 3;    // w0, w1, w2
-    static constexpr int E = 1;
-};
 
 struct PlaneArgs {
     const void *x, *w, *lam, *u, *dy;
@@ -205,8 +190,7 @@ __global__ __launch_bounds__(512, NB == 1 ? 4 : 2) void plane_kernel(const Plane
     const int nmine = max(0, min(NL, nvalid - q0));      // channels of this wave
     const int64_t pl0 = (int64_t)b * A.C + g * cpg + cfirst + (nmine > 0 ? q0 : 0);
     const int n = nmine * HW;                            // elements of this wave's stretch
-    // records of this wave's channels, with a spare one before and behind
-    const int rec0 = A.o_rec + wave * (NL * A.RS + 2 * N) + N;
+    const int rec0 = plane_wave_rec0(A.o_rec, wave, NL, A.RS, N);   // this wave's records
     const bool pm = A.pm != 0;
 
     // the records of zeros, the line of zero taps, the slots of absent channels
@@ -225,11 +209,8 @@ __global__ __launch_bounds__(512, NB == 1 ? 4 : 2) void plane_kernel(const Plane
     // copies derive from them is formed there instead of being kept in
     // registers over all directions
     int ln = lane, tid = (int)threadIdx.x;
-    // The record of pixel e of the wave's stretch: linear where rows are odd,
-    // else a record is left out behind each row (channels follow each other
-    // the same way).  With even rows planes begin at whole dwords, so a
-    // dword's two pixels lie in one row and their records side by side.
-    auto rec_of = [&](int e) { return rec0 + N * (e + (int)__umulhi((uint32_t)max(e, 0), A.mW)); };
+    // the record of pixel e of the wave's stretch
+    auto rec_of = [&](int e) { return rec0 + plane_rec(e, A.mW, N); };
     // ... and of element e of a blocked plane's stretch
     auto rec_of_blocked = [&](int e, bool vert, int L, int P) {
         int c = 0;
@@ -387,8 +368,7 @@ __global__ __launch_bounds__(512, NB == 1 ? 4 : 2) void plane_kernel(const Plane
             uint32_t va[M], vb[M];
 #pragma unroll
             for (int m = 0; m < M; ++m) {
-                // (a dword behind the stretch reads the spare record)
-                const uint32_t *r = lds + rec_of(min(E * (ln + 64 * (k0 + m)) - s.sh, s.n));
+                const uint32_t *r = lds + rec_of(plane_flush_pixel(E * (ln + 64 * (k0 + m)) - s.sh, s.n));
                 if constexpr (sizeof(S) == 4) {
                     va[m] = last ? r[N - 1] : r[2];
                     vb[m] = last ? 0u : r[3];
@@ -679,52 +659,9 @@ __global__ __launch_bounds__(256) void plane_dw_kernel(const float *__restrict__
     }
 }
 
-struct PlanePlan {
-    int NB, T, KB, cw, nwaves, nchunk, Wp, RS, o_w, o_sink, o_rec;
-    size_t lds;
-};
-
-PlanePlan plane_plan(const Problem &p, bool bwd)
+PlanePlan plan_of(const Problem &p, bool bwd)
 {
-    const int N = p.dtype == 0 ? Rec<float>::N : Rec<bf16_t>::N;
-    const int WN = p.dtype == 0 ? Rec<float>::WN : Rec<bf16_t>::WN;
-    const int m = std::max(p.H, p.W), HW = p.H * p.W, cpg = p.C / p.G;
-    PlanePlan q{};
-    q.NB = (m + 7) / 8;
-    q.T = m <= 16 ? 16 : (m <= 32 ? 32 : 64);
-    q.Wp = p.W | 1;
-    q.RS = p.H * q.Wp * N;
-    const int NL = 64 / q.T;
-    auto layout = [&](PlanePlan &r, int kb, int nw) {
-        const int slots = bwd ? kb * ((nw * NL + 3) & ~3) * q.T * 2 : 0;
-        r.KB = kb;
-        r.nwaves = nw;
-        r.o_w = slots;
-        r.o_sink = (r.o_w + (HW + m) * WN + 1) & ~1;
-        r.o_rec = r.o_sink + 64 * N;
-        r.lds = ((size_t)r.o_rec + (size_t)nw * (NL * q.RS + 2 * N)) * 4;
-        return r.lds <= (size_t)kLdsBytes;
-    };
-    PlanePlan best = q;
-    best.nchunk = 0;
-    for (int kb : {8, 4}) {
-        if (kb == 8 && q.T == 16)
-            continue;
-        PlanePlan r = q;
-        int nw = std::min(8, (cpg + NL - 1) / NL);
-        while (nw > 0 && !layout(r, kb, nw))
-            --nw;
-        if (nw == 0)
-            continue;
-        r.nchunk = (cpg + nw * NL - 1) / (nw * NL);
-        r.cw = (cpg + r.nchunk - 1) / r.nchunk;
-        layout(r, kb, (r.cw + NL - 1) / NL);
-        // the larger batch where its steps have a line of lanes each
-        if (best.nchunk == 0 || r.nchunk < best.nchunk ||
-            (r.nchunk == best.nchunk && best.nwaves * NL < best.KB))
-            best = r;
-    }
-    return best;
+    return plane_plan(p.H, p.W, p.C / p.G, p.dtype == 0, bwd);
 }
 
 template <int NB, typename S, bool BWD, int KB>
@@ -738,7 +675,7 @@ hipError_t plane_launch(const Problem &p, const PlanePlan &q, float *dwp, hipStr
     a.mask = p.mask, a.B = p.B, a.C = p.C, a.G = p.G, a.H = p.H, a.W = p.W;
     a.cw = q.cw, a.nchunk = q.nchunk, a.pm = p.layout == kPixelMajor;
     a.Wp = q.Wp, a.RS = q.RS;
-    a.mW = p.W % 2 == 0 ? (uint32_t)((((uint64_t)1 << 32) + p.W - 1) / p.W) : 0u;
+    a.mW = q.mW;
     a.mD = p.W > 1 ? (uint32_t)((((uint64_t)1 << 32) + p.W - 1) / p.W) : 0u;
     a.o_w = q.o_w, a.o_sink = q.o_sink, a.o_rec = q.o_rec;
     a.divChunk = make_magic((uint32_t)q.nchunk);
@@ -770,7 +707,7 @@ hipError_t plane_nb(const Problem &p, const PlanePlan &q, float *dwp, hipStream_
 template <typename S, bool BWD>
 hipError_t plane_t(const Problem &p, hipStream_t st)
 {
-    const PlanePlan q = plane_plan(p, BWD);
+    const PlanePlan q = plan_of(p, BWD);
     if (q.nchunk == 0)
         return hipErrorInvalidConfiguration;
     const int64_t ndw = (int64_t)__builtin_popcount(p.mask) * p.B * p.G * 3 * p.H * p.W;
@@ -806,7 +743,7 @@ hipError_t plane_t(const Problem &p, hipStream_t st)
 //    it always wins.
 bool plane_preferred(const Problem &p, bool bwd)
 {
-    const PlanePlan q = plane_plan(p, bwd);
+    const PlanePlan q = plan_of(p, bwd);
     if (q.nchunk == 0)
         return false;
     if (q.T == 16)
@@ -822,7 +759,7 @@ bool plane_preferred(const Problem &p, bool bwd)
 // Bytes of the backward's partial sums.
 int64_t plane_bwd_bytes(const Problem &p)
 {
-    const PlanePlan q = plane_plan(p, true);
+    const PlanePlan q = plan_of(p, true);
     return q.nchunk > 1 ? (int64_t)q.nchunk * __builtin_popcount(p.mask) * p.B * p.G * 3 * p.H *
                               p.W * (int64_t)sizeof(float)
                         : 0;
