@@ -477,6 +477,9 @@ __global__ __launch_bounds__(512, NB == 1 ? 4 : 2) void plane_kernel(const Plane
                         a = fmaf(in[i].tap(1), an, a);
                         a += from_right<T>(q0v);
                         a += from_left<T>(q2v);
+                        // (a zero tap times an infinite adjoint is a NaN: it
+                        // stays out of the idle lanes, which hand it back)
+                        a = act ? a : 0.f;
                         ahist[i] = a;
                         an = a;
                     }

@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 import gspn_inputs as gi
+import oracle
 import paper_2606_00746_amd as gspn
 from gpu_util import ignored_taps, require_gpu, to_host, upload
 from test_parity_gpu import GRAD_KEYS, case, check_against_oracle, run_gpu
@@ -87,6 +88,37 @@ def test_infinity_stays_in_its_channel(wl):
         assert np.array_equal(a, b), key
     ign = np.broadcast_to(ignored_taps(wl.dirs, wl.H, wl.W)[:, None, None], got["dw"].shape)
     assert np.all(got["dw"][ign] == 0.0)
+
+
+@pytest.mark.parametrize("wl", [case("adj-13x15", 4, 192, 16, 13, 15),
+                                case("adj-15x13-f32", 2, 96, 8, 15, 13, dtype="f32"),
+                                case("adj-28x28", 4, 192, 16, 28, 28),
+                                case("adj-25x29-f32", 4, 160, 32, 25, 29, dtype="f32"),
+                                case("adj-37x37", 2, 288, 144, 37, 37),
+                                case("adj-few-40x45", 1, 8, 2, 40, 45)], ids=lambda w: w.name)
+def test_infinite_adjoint_at_a_lines_end(wl):
+    """An infinite dy at the last position of the lines both ways (the corner):
+    the off-grid taps there are ignored, so infinities stay infinite, with the
+    oracle's sign, and nothing becomes NaN that is none by the equations (u, w
+    and lam are positive and x is made positive; the other channels of the
+    group keep their bits)."""
+    inputs = gi.make_inputs(wl, with_dy=True)
+    inputs["x"] = np.maximum(np.abs(inputs["x"]), np.float32(0.5))
+    clean = run_gpu(inputs, wl, True)
+    c = 5
+    dy = inputs["dy"].copy()
+    dy[0, c, wl.H - 1, wl.W - 1] = np.inf
+    got = run_gpu({**inputs, "dy": dy}, wl, True)
+    ref = oracle.scan_bwd(inputs["x"], inputs["w"], inputs["lam"], inputs["u"], dy, wl.dirs)
+    for k in GRAD_KEYS:
+        assert np.array_equal(np.isnan(got[k]), np.isnan(ref[k])), k
+        assert np.array_equal(got[k] == np.inf, ref[k] == np.inf), k
+        assert not np.isneginf(got[k]).any(), k
+    assert np.isinf(ref["dlam"][:, 0, c]).sum() > wl.H * wl.W
+    others = [k for k in range(wl.C) if k != c]
+    for k, axis in (("dx", 1), ("dlam", 2), ("du", 2)):
+        assert np.array_equal(np.take(got[k], others, axis=axis),
+                              np.take(clean[k], others, axis=axis)), k
 
 
 def test_caller_without_workspace():
