@@ -96,9 +96,9 @@ hipError_t dispatch_fwd(const Problem &p, hipStream_t s)
     if (p.H <= kSmallSide && p.W <= kSmallSide) {
         if (small_fwd_preferred(p))
             return launch_fwd_small(p, s);
-        if (!plane_preferred(p, false) && line_supported(p, false))
-            return launch_fwd_line(p, s);
-        return launch_fwd_plane(p, s);
+        if (plane_preferred(p, false))
+            return launch_fwd_plane(p, s);
+        return line_supported(p, false) ? launch_fwd_line(p, s) : launch_fwd_small(p, s);
     }
     const bool wide = wide_supported(p);
     if ((!wide || line_fwd_preferred(p)) && line_supported(p, false))
@@ -114,6 +114,8 @@ hipError_t dispatch_bwd(const Problem &p, hipStream_t s)
         return launch_bwd_tiny(p, s);
     if (p.H <= kSmallSide && p.W <= kSmallSide) {
         const bool plane = p.room(plane_bwd_bytes(p));
+        if (small_bwd_preferred(p))
+            return launch_bwd_small(p, s);
         if (!(plane && plane_preferred(p, true)) && line_supported(p, true))
             return launch_bwd_line(p, s);
         return plane ? launch_bwd_plane(p, s) : launch_bwd_small(p, s);

@@ -102,11 +102,13 @@ constexpr int kSmallSide = 64;
 constexpr int kLdsBytes = 160 * 1024;
 
 bool small_fwd_preferred(const Problem &p);
+bool small_bwd_preferred(const Problem &p);
 hipError_t launch_fwd_small(const Problem &p, hipStream_t s);
 hipError_t launch_bwd_small(const Problem &p, hipStream_t s);
 // Planes of any type and layout with both sides up to kSmallSide: whole planes
 // in LDS (scan_plane.hip).
 bool plane_preferred(const Problem &p, bool bwd);
+int plane_channels(const Problem &p, bool bwd);
 int64_t plane_bwd_bytes(const Problem &p);
 hipError_t launch_fwd_plane(const Problem &p, hipStream_t s);
 hipError_t launch_bwd_plane(const Problem &p, hipStream_t s);

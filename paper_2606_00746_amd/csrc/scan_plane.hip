@@ -662,7 +662,7 @@ __global__ __launch_bounds__(256) void plane_dw_kernel(const float *__restrict__
     }
 }
 
-PlanePlan plan_of(const Problem &p, bool bwd)
+PlanePlan plane_plan_of(const Problem &p, bool bwd)
 {
     return plane_plan(p.H, p.W, p.C / p.G, p.dtype == 0, bwd);
 }
@@ -710,7 +710,7 @@ hipError_t plane_nb(const Problem &p, const PlanePlan &q, float *dwp, hipStream_
 template <typename S, bool BWD>
 hipError_t plane_t(const Problem &p, hipStream_t st)
 {
-    const PlanePlan q = plan_of(p, BWD);
+    const PlanePlan q = plane_plan_of(p, BWD);
     if (q.nchunk == 0)
         return hipErrorInvalidConfiguration;
     const int64_t ndw = (int64_t)__builtin_popcount(p.mask) * p.B * p.G * 3 * p.H * p.W;
@@ -732,37 +732,63 @@ hipError_t plane_t(const Problem &p, hipStream_t st)
 
 }  // namespace
 
-// Where the plane family is the fastest (both sides at most 64; times in us,
-// forward / backward; line: scan_line.hip, small: scan_small.hip):
+// Channels that a CU holds at once.
+int plane_channels(const Problem &p, bool bwd)
+{
+    const PlanePlan q = plane_plan_of(p, bwd);
+    if (q.nchunk == 0)
+        return 0;
+    return (int)((size_t)kLdsBytes / q.lds) * std::min(q.cw, q.nwaves * (64 / q.T));
+}
+
+// Whether the plane family is faster than the line family, both sides at most
+// 64 (times in us, forward / backward; line: scan_line.hip; where neither is
+// wanted: small_fwd_preferred, small_bwd_preferred):
 //  * its time is that of the channels a CU holds: below 4 (waves of them in
 //    the forward) the line family's traffic costs less: bf16 50 x 50, 4
 //    channels, B*C = 3072: plane 136 / 317, line 135 / 406; 61 x 61, 2
 //    channels: 464 / 1115 and 202 / 745; fp32 37 x 37, 4 channels, B*C = 6144:
-//    222 / 467 and 265 / 905; fp32 40 x 56, 2 channels: 116 / 219 and 39 / 124;
+//    222 / 467 and 265 / 905; fp32 40 x 56, 2 channels: 116 / 219 and 39 / 124.
+//    A pixel-major forward with vertical directions, which line need not turn
+//    around, is line's up to 6: 51 x 33, T2B and B2T, G = C, 1468 planes: 68 and
+//    29; 41 x 41, four directions, G = C, 1216: 120 and 61; with those alone, in
+//    waves of two channels, up to 8: 31 x 31, 3 a group, 4020: 52 and 36; in
+//    fp32 up to 10, until some 8000 channels: 24 x 24, 1632: 27 and 18;
 //  * with few workgroups it is one workgroup's time, where the line family
 //    takes the directions and both sweeps side by side: 45 x 45, B*C = 256:
 //    38 / 104 and 27 / 85, B*C = 1024: 42 / 147 and 44 / 172; 28 x 28, B*C =
-//    64: 30 / 70 and 24 / 52, B*C = 1024: 30 / 89 and 32 / 134.  Up to 16 x 16
-//    it always wins.
+//    64: 30 / 70 and 24 / 52, B*C = 1024: 30 / 89 and 32 / 134; 33 x 51, G = C,
+//    224 (forward): 41 and 27 (one horizontal direction alone leaves nothing to
+//    run beside it: 42 x 35, 336 in 84 workgroups: 10 and 16).  Up to 16 x 16 it always wins, and in the
+//    backward below 250 pixels: 11 x 22, 120, 8 a group: 32 and 44.
 bool plane_preferred(const Problem &p, bool bwd)
 {
-    const PlanePlan q = plan_of(p, bwd);
+    const PlanePlan q = plane_plan_of(p, bwd);
     if (q.nchunk == 0)
         return false;
     if (q.T == 16)
         return true;
     const int per_cu = (int)((size_t)kLdsBytes / q.lds);
-    const int waves = per_cu * q.nwaves;
     const int64_t wgs = (int64_t)p.B * p.G * q.nchunk;
     if (bwd)
-        return per_cu * std::min(q.cw, q.nwaves * (64 / q.T)) >= 4 && wgs >= 32;
-    return waves >= 4 && wgs >= (q.T == 32 ? 64 : 128);
+        return (q.T == 32 && p.H * p.W < 250) || (plane_channels(p, true) >= 4 && wgs >= 32);
+    const bool turned = p.layout != kPixelMajor || (p.mask & 12) != 0;
+    if (q.T == 32) {
+        const int ch = plane_channels(p, false);
+        if (!turned)
+            return wgs >= 64 && (ch >= 10 || (ch >= 8 && (p.dtype == 1 || (int64_t)p.B * p.C >= 8000)));
+        return per_cu * q.nwaves >= 4 && wgs >= 64;
+    }
+    const bool horizontal = (p.mask & 3) == 0;
+    const bool one = p.layout == kPixelMajor && horizontal && p.mask != 12;
+    return per_cu * q.nwaves >= (horizontal || p.layout != kPixelMajor ? 4 : 6) &&
+           wgs >= (one ? 28 : 128) && (horizontal || wgs * q.nwaves >= 600);
 }
 
 // Bytes of the backward's partial sums.
 int64_t plane_bwd_bytes(const Problem &p)
 {
-    const PlanePlan q = plan_of(p, true);
+    const PlanePlan q = plane_plan_of(p, true);
     return q.nchunk > 1 ? (int64_t)q.nchunk * __builtin_popcount(p.mask) * p.B * p.G * 3 * p.H *
                               p.W * (int64_t)sizeof(float)
                         : 0;

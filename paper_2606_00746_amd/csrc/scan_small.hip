@@ -1,7 +1,8 @@
 // Register-resident line scans for planes with H, W <= 64, read from memory
-// step by step: the forward of few planes (small_fwd_preferred), and the
-// backward of callers whose workspace holds neither scan_plane.hip's partial
-// sums nor a round of scan_line.hip.
+// step by step: the forwards of small_fwd_preferred (few planes, blocked planes,
+// one channel a group), the backward of planes of a few pixels, and callers whose
+// workspace holds neither scan_plane.hip's partial sums nor a round of
+// scan_line.hip.
 //
 // One lane owns one position of a line (the perpendicular axis); a line of P
 // positions occupies T lanes (T = 16, 32 or 64, T >= P) and a wave holds
@@ -22,6 +23,8 @@
 // (all waves step in lock-step, one barrier per step) and written either as
 // the final dw or, when a group spans several workgroups, as an fp32 partial
 // that a second kernel sums in fixed order.
+#include <algorithm>
+
 #include "device.hpp"
 #include "launch.hpp"
 
@@ -395,16 +398,82 @@ int lanes_per_line(int H, int W)
 
 }  // namespace
 
-// The forward of few planes, which is one workgroup's time here as there: no
-// staging, the four directions side by side (us, small / plane / line): 28 x 28
-// bf16, B*C = 256: 17 / 30 / 23 (the call's host time), 1024: 25 / 30 / 32,
-// 12288: 217 / 109 / 258; fp32 1024: 38 / 33 / 30; 37 x 37 bf16 256: 23 / 30 /
-// 24, 1024: 64 / 31 / 42.
+// Where the forward here is the fastest of the three that take any plane up to 64
+// a side (times in us: small / plane / line).  It stages nothing and takes the
+// directions side by side, so with few planes it is one scan's latency, and its
+// loads are whole lines for vertical directions and blocked planes; pixel-major
+// horizontal ones (`gather`) touch a line of memory per lane.  `w`: its
+// workgroups, of one wave a direction.
+//  * up to 16 a side plane wins once its workgroups fill the chip and a wave's
+//    four channels are of one group: 13 x 13, four directions, G = C, w = 1024:
+//    18 / 25 / 96; 4 channels a group, w = 512: 11 / 13 / 43, 1024: 18 / 14 / 71; 2
+//    channels, w = 700: 14 / 14, 1100: 20 / 16; 15 x 15 blocked, 2, w = 5309: 84 /
+//    117;
+//  * pixel-major with horizontal directions: few planes up to 40 a side, 28 x 28
+//    bf16, B*C = 256: 14 / 27 / 16, 1024: 23 / 27 / 29, 12288: 208 / 87 / 249; fp32
+//    1024: 39 / 31 / 28; 37 x 37 bf16 256: 20 / 27 / 21, 1024: 73 / 28 / 38.  One
+//    direction alone gives the line family nothing to run side by side: 59 x 45
+//    L2R, 142 planes bf16: 14 / 18 / 17, fp32: 21 / 21 / 19;
+//  * otherwise up to 32 a side: vertical pixel-major bf16 until w = 900, or until
+//    two directions are 1552 waves (25 x 25, two, w = 700: 11 / 14 / 19, 900: 13 /
+//    14 / 23), and where plane holds under 8 channels a CU (31 x 31, 3 a group,
+//    two, w = 2010: 30 / 52 / 36); fp32 until w = 900, where plane holds under 10
+//    until 2000 (24 x 24, two, w = 816: 13 / 27 / 18, 2000: 27 / 33 / 29); blocked
+//    until w = 850 (28 x 27, 12 a group, four, w = 750: 36 / 48 / 62, 1500: 63 / 52 /
+//    95), and always where plane holds under 10 channels a CU, fp32 7 (31 x 31, 3 a
+//    group, four, w = 2010: 80 / 182 / 144); both where one or two waves share large
+//    planes' taps (28 x 28, 2 a group, two, w = 1920: pixel-major 27 / 40 / -,
+//    blocked 45 / 68 / -);
+//  * blocked up to 64, where line turns every plane around first: bf16 53 x 53,
+//    three directions, w = 224: 22 / 71 / 53; 47 x 47, four, w = 2112: 134 / 161 /
+//    131; planes that plane holds 6 or 8 of until w = 800 (44 x 28 L2R, 828: 24 /
+//    15 / 27).  fp32, whose planes are twice the bytes to turn, until one or two
+//    directions are 1400 waves and more 2200 (55 x 55, four, w = 216: 42 / 140 / 68;
+//    48 x 33, three, w = 1576: 118 / 182 / 165), but for large planes of several
+//    channels a group (64 x 64, four, 12 a group, w = 36: 52 / 130 / 39) or of few
+//    (56 x 56, four, 2: 46 / 98 / 33).
 bool small_fwd_preferred(const Problem &p)
 {
-    const int T = lanes_per_line(p.H, p.W);
-    const int64_t wgs = ((int64_t)p.B * p.C * T + 63) / 64;
-    return (p.H <= 40 && p.W <= 40) && wgs * (p.dtype == 0 ? 4 : 2) <= (T == 64 ? 512 : 1024);
+    const int T = lanes_per_line(p.H, p.W), cpg = p.C / p.G, HW = p.H * p.W;
+    const bool f32 = p.dtype == 0, pm = p.layout == kPixelMajor;
+    const int64_t w = ((int64_t)p.B * p.C * T + 63) / 64;
+    const int D = __builtin_popcount(p.mask);
+    const bool gather = pm && (p.mask & 12) != 0;
+    if (T == 16)
+        return cpg == 1 || w < 800 || (!pm && cpg < 4 && HW >= 190);
+    if (gather) {
+        if (T == 64 && D == 1)
+            return w <= (f32 ? 128 : 256);
+        return p.H <= 40 && p.W <= 40 && w * (f32 ? 4 : 2) <= (T == 64 ? 512 : 1024);
+    }
+    if (T == 32) {
+        const bool lone = cpg < 4 && HW >= 700;
+        const int ch = plane_channels(p, false);
+        if (pm)
+            return f32 ? w < 900 || (w < 2000 && ch < 10)
+                       : (w < 900 && w * D < 1552) || lone || ch < 8;
+        return w < 850 || lone || ch < (f32 ? 7 : 10);
+    }
+    if (pm)
+        return p.H <= 40 && p.W <= 40 && w * (f32 ? 4 : 2) <= 512;
+    if (f32)
+        return w * D < (D > 2 ? 2200 : 1400) && (D <= 2 || HW < 2400 || (cpg == 1 && w >= 100));
+    return w < 800 || HW >= 1800 || plane_channels(p, false) < (D > 2 ? 8 : 6);
+}
+
+// ... and the backward: planes of a few pixels, which plane's staging and
+// barriers exceed, of groups whose channels a step here takes in turn (small /
+// plane; line takes several times either): 1 x 1 T2B, B*C = 46326: 14 / 34, four
+// directions 36 / 86; 1 x 8 T2B, 58448: 14 / 33; 5 x 2, four, 4524 of G = C: 28 /
+// 38; 3 x 3, four, 2048, 4 a group: 17 / 18, 256, 32 a group: 30 / 22; 3 x 1 L2R
+// and R2L, 19296, 32 a group: 11 / 25; 4 x 4, four, 512: 20 / 17; 1 x 8 L2R and
+// R2L, 32: 34 / 16; 5 x 4 T2B, 2000: 8.1 / 8.1.
+bool small_bwd_preferred(const Problem &p)
+{
+    const int HW = p.H * p.W, m = p.H > p.W ? p.H : p.W;
+    const int steps = std::max((p.mask & 3) ? p.H : 0, (p.mask & 12) ? p.W : 0);
+    const bool few = __builtin_popcount(p.mask) == 1 ? HW <= 20 && m <= 16 : HW < 12 && m <= 5;
+    return few && (int64_t)(p.C / p.G) * steps <= 64;
 }
 
 hipError_t launch_fwd_small(const Problem &p, hipStream_t st)

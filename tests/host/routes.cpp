@@ -1,0 +1,103 @@
+// The kernel family of planes up to 64 a side, for calls timed in every family (us,
+// small / plane / line): each goes to one that is at most 5% behind the fastest.
+#include <cstdio>
+
+#include "launch.hpp"
+
+using namespace gspn;
+
+struct Call {
+    bool bwd, blocked;
+    int H, W, B, C, G, dtype, mask;
+    float us[3];
+};
+
+// H, W, B, C, G, dtype, direction mask, times.  About half of them had been sent to a
+// family 1.3 times slower or more.
+static const Call calls[] = {
+    {true, false, 9, 9, 8, 6, 3, 0, 15, {38.5f, 19.5f, 28.9f}},
+    {true, false, 2, 2, 2, 54, 18, 0, 15, {12.7f, 16.6f, 35.6f}},
+    {true, false, 1, 2, 4, 21, 21, 0, 3, {5.6f, 9.9f, 11.4f}},
+    {true, false, 13, 13, 2, 16, 4, 1, 15, {58.2f, 27.3f, 43.8f}},
+    {true, false, 2, 2, 3, 1, 1, 1, 12, {6.9f, 9.8f, 14.9f}},
+    {true, false, 2, 3, 2, 102, 51, 1, 1, {4.8f, 7.1f, 11.0f}},
+    {true, false, 22, 22, 2, 840, 70, 0, 1, {41.2f, 17.0f, 42.1f}},
+    {true, false, 11, 22, 1, 84, 7, 0, 4, {37.4f, 12.9f, 27.7f}},
+    {true, false, 20, 11, 4, 24, 2, 0, 15, {98.7f, 34.9f, 65.7f}},
+    {true, false, 28, 28, 1, 1896, 474, 1, 7, {144.6f, 49.8f, 76.7f}},
+    {true, false, 13, 17, 8, 24, 3, 1, 15, {78.7f, 31.2f, 49.6f}},
+    {true, false, 10, 19, 2, 32, 1, 1, 4, {35.8f, 15.2f, 25.2f}},
+    {true, false, 63, 63, 1, 104, 13, 0, 3, {190.8f, 110.3f, 41.5f}},
+    {true, false, 62, 34, 1, 1636, 1636, 1, 15, {1194.8f, 555.0f, 273.7f}},
+    {true, true, 7, 8, 12, 2, 1, 0, 15, {31.7f, 17.1f, 52.0f}},
+    {true, true, 1, 1, 8, 2, 2, 0, 15, {8.6f, 12.8f, 42.5f}},
+    {true, true, 1, 1, 1, 10128, 1266, 0, 4, {5.4f, 7.7f, 120.0f}},
+    {true, true, 10, 10, 1, 3, 1, 1, 15, {42.2f, 28.1f, 55.2f}},
+    {true, true, 1, 1, 1, 3136, 98, 1, 7, {11.3f, 16.9f, 98.9f}},
+    {true, true, 1, 1, 32, 82, 41, 1, 1, {4.5f, 8.3f, 35.8f}},
+    {true, true, 16, 23, 1, 10248, 854, 0, 7, {519.5f, 201.3f, 541.7f}},
+    {true, true, 11, 22, 1, 120, 15, 0, 1, {20.6f, 12.8f, 28.5f}},
+    {true, true, 22, 11, 1, 2, 2, 0, 12, {27.6f, 17.7f, 27.6f}},
+    {true, true, 22, 22, 8, 1100, 550, 1, 15, {444.6f, 273.4f, 610.7f}},
+    {true, true, 11, 20, 1, 3, 1, 1, 15, {66.2f, 39.8f, 56.0f}},
+    {true, true, 11, 19, 2, 3, 1, 1, 7, {45.7f, 30.1f, 47.5f}},
+    {true, true, 37, 61, 1, 2, 1, 0, 15, {249.7f, 130.7f, 75.5f}},
+    {true, true, 59, 56, 4, 2, 2, 1, 7, {254.5f, 172.6f, 49.2f}},
+    {false, false, 13, 13, 1, 328, 41, 0, 1, {4.4f, 6.5f, 7.3f}},
+    {false, false, 15, 15, 2, 832, 26, 0, 15, {13.2f, 23.6f, 34.6f}},
+    {false, false, 8, 12, 8, 208, 26, 0, 7, {6.8f, 8.8f, 24.5f}},
+    {false, false, 8, 7, 4, 12, 1, 1, 15, {6.2f, 9.3f, 11.4f}},
+    {false, false, 14, 15, 8, 462, 462, 1, 1, {6.6f, 10.9f, 17.0f}},
+    {false, false, 14, 8, 32, 98, 98, 1, 3, {6.4f, 10.6f, 20.3f}},
+    {false, false, 20, 31, 2, 668, 334, 0, 12, {35.6f, 17.6f, 33.2f}},
+    {false, false, 19, 19, 4, 228, 19, 0, 3, {9.1f, 12.4f, 11.9f}},
+    {false, false, 32, 32, 1, 1312, 41, 0, 1, {9.6f, 13.2f, 13.4f}},
+    {false, false, 10, 17, 2, 9960, 1245, 1, 15, {149.3f, 44.7f, 294.3f}},
+    {false, false, 25, 27, 4, 306, 153, 1, 3, {11.4f, 15.0f, 18.2f}},
+    {false, false, 62, 46, 1, 1, 1, 0, 7, {20.7f, 48.7f, 14.7f}},
+    {false, false, 38, 38, 8, 160, 5, 0, 3, {35.4f, 40.7f, 21.5f}},
+    {false, false, 32, 41, 4, 384, 48, 0, 3, {36.6f, 37.3f, 20.8f}},
+    {false, false, 37, 37, 1, 574, 287, 1, 4, {21.0f, 11.2f, 20.6f}},
+    {false, false, 30, 44, 1, 374, 187, 1, 3, {15.6f, 15.0f, 11.3f}},
+    {false, false, 46, 46, 4, 92, 46, 1, 15, {55.5f, 44.8f, 25.3f}},
+    {false, true, 6, 10, 32, 336, 84, 0, 15, {36.0f, 19.4f, 125.2f}},
+    {false, true, 1, 1, 4, 536, 536, 0, 3, {5.0f, 7.2f, 21.6f}},
+    {false, true, 14, 14, 32, 624, 624, 0, 1, {38.8f, 68.4f, 102.4f}},
+    {false, true, 8, 14, 1, 14672, 7336, 1, 15, {58.0f, 41.4f, 188.0f}},
+    {false, true, 12, 15, 8, 352, 11, 1, 7, {14.0f, 21.2f, 49.4f}},
+    {false, true, 12, 15, 2, 1923, 1923, 1, 4, {7.8f, 11.6f, 36.0f}},
+    {false, true, 32, 32, 4, 10, 5, 0, 7, {20.4f, 41.4f, 26.7f}},
+    {false, true, 30, 30, 2, 294, 147, 0, 3, {20.4f, 30.4f, 33.9f}},
+    {false, true, 32, 32, 2, 297, 297, 0, 15, {46.9f, 106.1f, 68.1f}},
+    {false, true, 13, 26, 2, 4960, 155, 1, 4, {44.1f, 22.0f, 72.4f}},
+    {false, true, 27, 29, 1, 4552, 569, 1, 15, {87.7f, 149.0f, 131.6f}},
+    {false, true, 30, 30, 32, 41, 41, 1, 15, {36.0f, 96.0f, 88.2f}},
+    {false, true, 29, 37, 8, 15, 15, 0, 15, {24.8f, 42.1f, 42.1f}},
+    {false, true, 44, 44, 1, 32, 1, 0, 1, {11.0f, 17.1f, 14.9f}},
+    {false, true, 57, 59, 1, 4, 1, 0, 4, {14.7f, 32.8f, 19.4f}},
+    {false, true, 21, 38, 8, 128, 4, 1, 7, {41.8f, 25.5f, 44.3f}},
+    {false, true, 41, 41, 7, 3, 1, 1, 7, {17.2f, 35.2f, 29.9f}},
+    {false, true, 32, 43, 1, 64, 2, 1, 15, {21.9f, 46.6f, 36.6f}},
+};
+
+int main()
+{
+    int bad = 0;
+    for (const Call &c : calls) {
+        Problem p{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                  nullptr, c.mask, c.B, c.C, c.G, c.H, c.W, c.dtype, c.blocked ? kBlocked : kPixelMajor};
+        const bool small = c.bwd ? small_bwd_preferred(p) : small_fwd_preferred(p);
+        const int family = small ? 0 : plane_preferred(p, c.bwd) ? 1 : 2;
+        float best = c.us[0];
+        for (float t : c.us)
+            best = t < best ? t : best;
+        if (c.us[family] > 1.05f * best + 0.3f) {
+            printf("%s%s %dx%d B=%d C=%d G=%d dtype %d mask %d: family %d, %.1f of %.1f us\n",
+                   c.bwd ? "bwd" : "fwd", c.blocked ? "_blocked" : "", c.H, c.W, c.B, c.C, c.G,
+                   c.dtype, c.mask, family, c.us[family], best);
+            ++bad;
+        }
+    }
+    printf(bad ? "%d calls on a slower family\n" : "all routes clean\n", bad);
+    return bad != 0;
+}

@@ -1,5 +1,6 @@
 """Host-side code of libgspn, built and run on the CPU: the index functions that
-the kernels share with the host, over every size they take."""
+the kernels share with the host, over every size they take, and the choice of the
+kernel family."""
 import os
 import subprocess
 
@@ -22,3 +23,9 @@ def _build_and_run(tmp_path, name, *link):
 
 def test_plane_records_stay_inside_lds(tmp_path):
     assert "all plans clean" in _build_and_run(tmp_path, "plane_lds")
+
+
+def test_routes_follow_the_measured_times(tmp_path):
+    assert "all routes clean" in _build_and_run(tmp_path, "routes", os.path.join(
+        ROOT, "paper_2606_00746_amd", "libgspn.so"),
+        "-Wl,-rpath," + os.path.join(ROOT, "paper_2606_00746_amd"))
