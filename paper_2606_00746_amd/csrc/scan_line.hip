@@ -900,6 +900,20 @@ constexpr int64_t kRoundBytes = (int64_t)512 << 20;
 constexpr int64_t kSmallBytes = (int64_t)1 << 20;
 constexpr int64_t kPartPad = 64 * 256;           // alignment of a round's parts
 
+// A small workspace cuts a call into rounds of a group or a few, each with its
+// own launches and its own chain of steps.  They are taken where a round still
+// has two waves a CU, or where there are so few of them that all planes at once in
+// the general family, whose time is its steps, take longer: in the backward up to
+// kFewRounds; in the forward one for so many steps (kRoundSteps: vertical
+// pixel-major directions alone, which turn nothing around; pixel-major; blocked,
+// where every tensor of a direction is a launch).  us, rounds / general: T2B and B2T,
+// 70 x 70, two rounds: 28 / 52, 114 x 114, three: 41 / 81, 21 x 137, two: 27 / 18;
+// 62 x 88, two, four directions: 45 / 81, 22 x 145, four, R2L: 151 / 93; blocked 77
+// x 77, 8, four directions: 159 / 60, 28 x 154, four: 230 / 97.
+constexpr int64_t kFullWaves = 512;
+constexpr int64_t kFewRounds = 4;
+constexpr int kRoundSteps[3] = {16, 37, 60};
+
 // What a call of the general family takes; planes of at most 64 have other
 // fallbacks, which take less.
 int64_t general_bytes(const Problem &p, bool bwd)
@@ -960,6 +974,13 @@ LinePlan line_plan(const Problem &p, bool bwd)
         most = gen;
     q.fits = one <= most && gen <= most;
     q.ru = std::max<int64_t>(1, std::min(q.units, (most - kPartPad) / q.unit_bytes));
+    // rounds follow each other on the stream
+    const int64_t rounds = (q.units + q.ru - 1) / q.ru;
+    const int64_t waves = q.ru * q.cpg * q.D * (bwd ? 2 : 1);
+    const int steps = std::max(nv ? p.H : 0, q.nh ? p.W : 0);
+    const int kind = p.layout != kPixelMajor ? 2 : (q.nh || q.rows_x ? 1 : 0);
+    q.fits = q.fits && (rounds == 1 || waves >= kFullWaves ||
+                        (bwd ? rounds <= kFewRounds : rounds * kRoundSteps[kind] <= steps));
     q.bytes = std::max(gen, q.ru * q.unit_bytes + kPartPad);
     return q;
 }
@@ -1175,8 +1196,14 @@ hipError_t line_t(const Problem &p, bool bwd, hipStream_t st)
 
 }  // namespace
 
+// (Blocked forwards of a few steps are the launches that turn their planes into
+// rows: line / general, us: 12 x 118, T2B and B2T, B*C = 64: 17 / 11; 16 x 68, 19: 18 /
+// 14; 19 x 76, 32: 14 / 17.)
 bool line_supported(const Problem &p, bool bwd)
 {
+    const int steps = std::max((p.mask & 3) ? p.H : 0, (p.mask & 12) ? p.W : 0);
+    if (!bwd && p.layout != kPixelMajor && steps <= 16)
+        return false;
     return (p.H > p.W ? p.H : p.W) <= kLineSide && line_plan(p, bwd).fits;
 }
 

@@ -80,9 +80,44 @@ static const Call calls[] = {
     {false, true, 32, 43, 1, 64, 2, 1, 15, {21.9f, 46.6f, 36.6f}},
 };
 
+// Planes above 64 a side: line family in rounds of what the query's workspace holds /
+// general family.
+struct LongCall {
+    bool bwd, blocked;
+    int H, W, B, C, G, dtype, mask;
+    float line, general;
+};
+
+static const LongCall long_calls[] = {
+    {false, true, 68, 34, 18, 1, 1, 1, 15, 146.8f, 43.2f},
+    {false, true, 47, 65, 3, 8, 1, 1, 8, 81.6f, 42.1f},
+    {false, true, 43, 69, 2, 10, 5, 1, 8, 106.0f, 45.4f},
+    {false, true, 26, 146, 8, 1, 1, 1, 1, 61.2f, 20.2f},
+    {false, true, 102, 63, 1, 14, 14, 1, 3, 138.0f, 65.2f},
+    {false, true, 12, 118, 2, 32, 2, 1, 3, 17.1f, 11.2f},
+    {false, true, 16, 68, 19, 1, 1, 1, 3, 17.7f, 13.9f},
+    {false, false, 22, 145, 1, 8, 4, 1, 8, 150.7f, 92.7f},
+    {false, false, 31, 95, 2, 14, 14, 1, 4, 119.7f, 72.9f},
+    {false, false, 77, 150, 2, 3, 3, 1, 4, 223.6f, 135.1f},
+    {false, false, 21, 137, 2, 8, 1, 1, 3, 27.1f, 18.4f},
+    {false, false, 70, 70, 2, 1, 1, 1, 3, 28.1f, 51.8f},
+    {false, false, 114, 114, 3, 1, 1, 1, 3, 41.3f, 81.2f},
+    {false, false, 40, 110, 1, 8, 2, 1, 15, 50.6f, 92.5f},
+};
+
 int main()
 {
     int bad = 0;
+    for (const LongCall &c : long_calls) {
+        Problem p{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                  nullptr, c.mask, c.B, c.C, c.G, c.H, c.W, c.dtype, c.blocked ? kBlocked : kPixelMajor};
+        if (line_supported(p, c.bwd) != (c.line < c.general)) {
+            printf("%s%s %dx%d B=%d C=%d G=%d dtype %d mask %d: line %.1f, general %.1f us\n",
+                   c.bwd ? "bwd" : "fwd", c.blocked ? "_blocked" : "", c.H, c.W, c.B, c.C, c.G,
+                   c.dtype, c.mask, c.line, c.general);
+            ++bad;
+        }
+    }
     for (const Call &c : calls) {
         Problem p{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                   nullptr, c.mask, c.B, c.C, c.G, c.H, c.W, c.dtype, c.blocked ? kBlocked : kPixelMajor};
