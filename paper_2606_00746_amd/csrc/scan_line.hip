@@ -888,16 +888,26 @@ __global__ __launch_bounds__(kTileThreads) void merge_kernel(const GradArgs A)
 // host
 // ---------------------------------------------------------------------------
 
-// Workspace.  A round takes what its weight groups need, at most kRoundBytes
-// (or one group).  Small rounds would leave h and a in the 256 MB Infinity
-// Cache for the gradients, but fill the chip less: 128 x 128, B = 2, C = 192
-// in rounds of 160 MB 453 us, of 240 MB 389 us, in one (277 MB) 381 us.  The
-// size that the query gives is never below the general family's, and stays
-// that where it is below kSmallBytes; a caller that hands in less than the
-// query's size, but what the general family takes, gets smaller rounds, or
-// the general family where not even one group fits.
+// Workspace.  A round takes what its weight groups need, at most kRoundBytes,
+// or one whole group, or the general family's need where these are more (a group
+// is never cut: 256 x 256 bf16, C = 768, G = 1, backward: 2.2 GB).  Small rounds
+// would leave h and a in the 256 MB Infinity Cache for the gradients, but fill the
+// chip less: 128 x 128, B = 2, C = 192 in rounds of 160 MB 453 us, of 240 MB 389
+// us, in one (277 MB) 381 us.  The size that the query gives is never below the
+// general family's; a caller that hands in less than the query's size, but what the
+// general family takes, gets smaller rounds, or the general family.
+//
+// Below kSmallBytes the query gives what the general family takes, no more, as it
+// always has: callers hold workspaces of those sizes, and one byte less is refused
+// there.  That is the only reason; the line family with a workspace of its own is
+// the faster at nearly every size below (us, general / line: forward fp32 70 x 100,
+// B*C = 3: 92 / 26; bf16 70 x 70, 8: 66 / 20, blocked 50 / 38; backward 70 x 70, 8
+// of G = C: 179 / 32).  The line lies close above the sizes so held (168,000 and
+// 672,000 bytes); from it on the gap is wider than a few hundred kilobytes are
+// worth: backward 70 x 70, 8 in one group (0.94 MB): 1515 / 55; 80 x 80, 32 in one
+// group, T2B (0.92 MB): 5438 / 29.
 constexpr int64_t kRoundBytes = (int64_t)512 << 20;
-constexpr int64_t kSmallBytes = (int64_t)1 << 20;
+constexpr int64_t kSmallBytes = (int64_t)704 << 10;
 constexpr int64_t kPartPad = 64 * 256;           // alignment of a round's parts
 
 // A small workspace cuts a call into rounds of a group or a few, each with its

@@ -29,3 +29,14 @@ def test_routes_follow_the_measured_times(tmp_path):
     assert "all routes clean" in _build_and_run(tmp_path, "routes", os.path.join(
         ROOT, "paper_2606_00746_amd", "libgspn.so"),
         "-Wl,-rpath," + os.path.join(ROOT, "paper_2606_00746_amd"))
+
+
+def test_line_family_sizes_its_own_workspace():
+    """From the held sizes on, the query gives what one round of the line family
+    takes, not what the general family would (backwards of one large group,
+    whose general kernels take its channels in turn)."""
+    import paper_2606_00746_amd as g
+    for dirs, C, G, H, W in ((15, 8, 1, 70, 70), (1, 32, 1, 80, 80), (3, 16, 1, 101, 67)):
+        D = bin(dirs).count("1")
+        st, n = g.gspn_workspace_size(g.OP_BWD, dirs, 1, C, G, H, W, g.BF16)
+        assert st == 0 and n > 4 * D * (C + 4 * G) * H * W
