@@ -98,6 +98,9 @@ inline hipError_t take_reserve(const Problem &p, ReserveParts *r)
 // Planes whose sides are both <= kSmallSide run on the register-resident path.
 constexpr int kSmallSide = 64;
 
+// Threads a launch may have in all (the packet's grid size is 32 bits).
+constexpr int64_t kMaxThreads = 0xffffffffll;
+
 // LDS a workgroup may use on gfx950 (the only target of this library).
 constexpr int kLdsBytes = 160 * 1024;
 

@@ -984,6 +984,11 @@ LinePlan line_plan(const Problem &p, bool bwd)
         most = gen;
     q.fits = one <= most && gen <= most;
     q.ru = std::max<int64_t>(1, std::min(q.units, (most - kPartPad) / q.unit_bytes));
+    // (the merge has kTileThreads a tile of every plane, the other launches up to
+    // twice that a plane)
+    const int64_t max_planes = kMaxThreads / (2 * kTileThreads * tiles);
+    q.fits = q.fits && q.cpg <= max_planes;
+    q.ru = std::max<int64_t>(1, std::min(q.ru, max_planes / q.cpg));
     // rounds follow each other on the stream
     const int64_t rounds = (q.units + q.ru - 1) / q.ru;
     const int64_t waves = q.ru * q.cpg * q.D * (bwd ? 2 : 1);

@@ -439,6 +439,8 @@ bool small_fwd_preferred(const Problem &p)
     const int64_t w = ((int64_t)p.B * p.C * T + 63) / 64;
     const int D = __builtin_popcount(p.mask);
     const bool gather = pm && (p.mask & 12) != 0;
+    if (w > kMaxThreads / 256)
+        return false;
     if (T == 16)
         return cpg == 1 || w < 800 || (!pm && cpg < 4 && HW >= 190);
     if (gather) {

@@ -1027,7 +1027,8 @@ bool wide_supported(const Problem &p)
 bool wide_sum_supported(const Problem &p)
 {
     return p.layout != kPixelMajor && wide_supported(p) &&
-           wide_sum_lds(p.H, p.W) <= (size_t)kLdsBytes;
+           wide_sum_lds(p.H, p.W) <= (size_t)kLdsBytes &&
+           (int64_t)p.B * p.C <= kMaxThreads / 256;      // one workgroup a plane
 }
 
 hipError_t launch_fwd_wide_sum(const Problem &p, hipStream_t st)

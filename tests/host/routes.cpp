@@ -105,9 +105,36 @@ static const LongCall long_calls[] = {
     {false, false, 40, 110, 1, 8, 2, 1, 15, 50.6f, 92.5f},
 };
 
-int main()
+// Calls whose single launch in the family would have 2^32 threads or more, which HIP
+// refuses, and the largest that have fewer: taken by the family or not.
+static int check_launch_limits()
 {
     int bad = 0;
+    auto problem = [](int mask, int C, int G, int H, int W, int layout) {
+        return Problem{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                       nullptr, mask, 1, C, G, H, W, 1, layout};
+    };
+    auto expect = [&](bool got, bool want, const char *what) {
+        if (got != want) {
+            printf("launch limits: %s\n", what);
+            ++bad;
+        }
+    };
+    // a plane of 8 x 16 pixels is 256 threads of the sum in LDS
+    expect(wide_sum_supported(problem(1, (1 << 24) - 1, 1, 8, 16, kBlocked)), true, "sums");
+    expect(wide_sum_supported(problem(1, 1 << 24, 1, 8, 16, kBlocked)), false, "too many sums");
+    // one group of 65 x 65 planes, 6 tiles of 512 threads each
+    expect(line_supported(problem(1, 1 << 19, 1, 65, 65, kPixelMajor), false), true, "a group");
+    expect(line_supported(problem(1, 1 << 21, 1, 65, 65, kPixelMajor), false), false, "too large a group");
+    // the small forward: 256 threads for every four planes
+    expect(small_fwd_preferred(problem(1, (1 << 26) - 4, (1 << 26) - 4, 9, 9, kPixelMajor)), true, "small");
+    expect(small_fwd_preferred(problem(1, 1 << 26, 1 << 26, 9, 9, kPixelMajor)), false, "too many small");
+    return bad;
+}
+
+int main()
+{
+    int bad = check_launch_limits();
     for (const LongCall &c : long_calls) {
         Problem p{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                   nullptr, c.mask, c.B, c.C, c.G, c.H, c.W, c.dtype, c.blocked ? kBlocked : kPixelMajor};
