@@ -313,9 +313,22 @@ def workspace_size(op, x, w, direction) -> int:
     return n
 
 
+_get_device = None
+
+
+def _current_device() -> int:
+    """The device whose plan a query gives and a call takes: the current one,
+    whichever the tensors are on."""
+    global _get_device
+    if _get_device is None:
+        import torch
+        _get_device = torch._C._cuda_getDevice
+    return _get_device()
+
+
 @functools.lru_cache(maxsize=256)
 def _workspace_bytes(op, direction, B, C, G, H, W, dtype, slots, device):
-    """The size query, asked once per sizes and device."""
+    """The size query, asked once per sizes and current device."""
     st, n = (gspn_workspace_size_slots(slots, direction, B, C, G, H, W, dtype) if slots
              else gspn_workspace_size(op, direction, B, C, G, H, W, dtype))
     _check_raise(st)
@@ -326,7 +339,7 @@ def _workspace(op, direction, B, C, G, H, W, dtype, device, given=None, slots=0)
     """The device buffer operation `op` works in: `given` (a uint8 tensor on
     the same device) when it is large enough, else a new one (None if the
     call needs none)."""
-    n = _workspace_bytes(op, direction, B, C, G, H, W, dtype, slots, device)
+    n = _workspace_bytes(op, direction, B, C, G, H, W, dtype, slots, _current_device())
     if n == 0:
         return None, 0
     import torch
@@ -426,12 +439,12 @@ def reserve_size(x, w, direction, norm: bool = False) -> int:
     """Bytes of the reserve of the training pair for these tensors (norm: the
     pair of the _norm entry points, w holding the logits)."""
     B, C, G, H, W = _sizes(x, w, direction)
-    return _reserve_bytes(norm, direction, B, C, G, H, W, _dtype_code(x), x.device)
+    return _reserve_bytes(norm, direction, B, C, G, H, W, _dtype_code(x), _current_device())
 
 
 @functools.lru_cache(maxsize=256)
 def _reserve_bytes(norm, direction, B, C, G, H, W, dtype, device):
-    """The reserve's size query, asked once per sizes and device."""
+    """The reserve's size query, asked once per sizes and current device."""
     st, n = (gspn_reserve_size_norm if norm else gspn_reserve_size)(direction, B, C, G, H, W,
                                                                      dtype)
     _check_raise(st)

@@ -40,3 +40,26 @@ def test_line_family_sizes_its_own_workspace():
         D = bin(dirs).count("1")
         st, n = g.gspn_workspace_size(g.OP_BWD, dirs, 1, C, G, H, W, g.BF16)
         assert st == 0 and n > 4 * D * (C + 4 * G) * H * W
+
+
+def test_sizes_are_kept_per_current_device(monkeypatch):
+    """The binding asks the library for a call's workspace (and reserve) once per
+    sizes and device: the current device, on which the plan is made."""
+    import torch
+
+    from paper_2606_00746_amd import _native as n
+    device = [0]
+    monkeypatch.setattr(n, "_get_device", lambda: device[0], raising=False)
+    monkeypatch.setattr(n, "gspn_workspace_size", lambda *a: (0, 1000 + device[0]))
+    monkeypatch.setattr(n, "gspn_reserve_size", lambda *a: (0, 2000 + device[0]))
+    x, w = torch.empty(1, 4, 99, 98), torch.empty(1, 1, 2, 3, 99, 98)
+    on = torch.device("cpu")
+    n._workspace_bytes.cache_clear()
+    n._reserve_bytes.cache_clear()
+    try:
+        for device[0] in (0, 1, 0):
+            assert n._workspace(0, 1, 1, 4, 2, 99, 98, 0, on)[1] == 1000 + device[0]
+            assert n.reserve_size(x, w, 1) == 2000 + device[0]
+    finally:
+        n._workspace_bytes.cache_clear()
+        n._reserve_bytes.cache_clear()
