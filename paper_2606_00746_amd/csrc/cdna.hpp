@@ -236,8 +236,11 @@ __device__ __forceinline__ void st_piece(const u32x4 &d, int j, int q, int P, in
     }
 }
 
-// Product and sum that the compiler may not fuse into a multiply-add (the
-// direction sums of the forwards round u_d * h_d, then add, in every layout).
+// Product and sum that the compiler may not fuse into a multiply-add: the
+// direction sums of the plane, line and wide forwards round u_d * h_d, then add.
+// They add in direction-bit order, except where blocked planes are summed in LDS
+// (fwd_wide_sum_kernel), which adds in the order of its turns: there the layouts
+// may differ in the last bit of the fp32 sum of three or four directions.
 __device__ __forceinline__ float mul_nc(float a, float b)
 {
 #pragma clang fp contract(off)

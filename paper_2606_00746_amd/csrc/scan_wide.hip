@@ -237,7 +237,7 @@ __device__ __forceinline__ void wide_dir(int lane, int H_, int W_, rsrc_t lam, r
             if (MODE == kSum) {
 #pragma unroll
                 for (int m = 0; m < NPL; ++m)
-                    v[m][e] = elem(pc.u[m], e) * h[m];
+                    v[m][e] = mul_nc(elem(pc.u[m], e), h[m]);
                 if (!HC && NPL <= 2)
                     step_fence();     // keeps the registers at 3 waves per SIMD
             }
@@ -257,7 +257,7 @@ __device__ __forceinline__ void wide_dir(int lane, int H_, int W_, rsrc_t lam, r
                     if (valid[m]) {
 #pragma unroll
                         for (int e = 0; e < 8; ++e)
-                            v[m][e] += a[e * st];
+                            v[m][e] = add_nc(a[e * st], v[m][e]);
 #pragma unroll
                         for (int e = 0; e < 8; ++e)
                             a[e * st] = v[m][e];

@@ -3,7 +3,9 @@ oracle: sides of one block of 8 lines, of odd block counts (two opposite scans
 meet in the middle block) both ways, one way and neither way, scans of unequal
 length, lines of 1 to 4 positions per lane, direction subsets without
 opposite or crossing scans, and the largest sums LDS holds next to the first
-that it does not.  Two runs give the same bits, and no workspace is taken."""
+that it does not.  Two runs give the same bits, and no workspace is taken.  With
+one or two directions, whose sum has no order, the pixel-major call gives the same
+bits too: both layouts round u * h and then add."""
 import pytest
 
 import gspn_inputs as gi
@@ -40,5 +42,9 @@ def test_sum_in_lds(wl):
     a, b = (gspn.scan_fwd(t["x"], t["w"], t["lam"], t["u"], wl.dirs, layout="blocked")
             for _ in range(2))
     assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    if bin(wl.dirs).count("1") <= 2:
+        pm = upload(inputs, wl.dtype, wl.dirs)
+        c = gspn.scan_fwd(pm["x"], pm["w"], pm["lam"], pm["u"], wl.dirs)
+        assert torch.equal(a.view(torch.int16), c.view(torch.int16))
     n = gspn.workspace_size(gspn.OP_FWD_BLOCKED, t["x"], t["w"], wl.dirs)
     assert (n == 0) == wl.name.startswith("sum")
