@@ -250,10 +250,21 @@ def _dtype_code(t) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}; use float32 or bfloat16")
 
 
+# torch's own getters, looked up at the first call (the package imports without torch)
+_get_device = _get_stream = None
+
+
+def _bind_torch():
+    global _get_device, _get_stream
+    import torch
+    _get_device, _get_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+
+
 def _stream_handle(t, stream):
     if stream is None:
-        import torch
-        return torch._C._cuda_getCurrentRawStream(t.get_device())
+        if _get_stream is None:
+            _bind_torch()
+        return _get_stream(t.get_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -313,16 +324,11 @@ def workspace_size(op, x, w, direction) -> int:
     return n
 
 
-_get_device = None
-
-
 def _current_device() -> int:
     """The device whose plan a query gives and a call takes: the current one,
     whichever the tensors are on."""
-    global _get_device
     if _get_device is None:
-        import torch
-        _get_device = torch._C._cuda_getDevice
+        _bind_torch()
     return _get_device()
 
 
