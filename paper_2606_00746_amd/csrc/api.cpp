@@ -100,7 +100,7 @@ hipError_t dispatch_fwd(const Problem &p, hipStream_t s)
             return launch_fwd_plane(p, s);
         return line_supported(p, false) ? launch_fwd_line(p, s) : launch_fwd_small(p, s);
     }
-    const bool wide = wide_supported(p);
+    const bool wide = wide_supported(p) && (p.ws_cap < 0 || p.room(wide_fwd_bytes(p)));
     if ((!wide || line_fwd_preferred(p)) && line_supported(p, false))
         return launch_fwd_line(p, s);
     return wide ? launch_fwd_wide(p, s) : launch_fwd_general(p, s);

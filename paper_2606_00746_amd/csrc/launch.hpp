@@ -158,6 +158,7 @@ hipError_t launch_fwd_pm(const Problem &p, hipStream_t s);
 // at wb), for the register-streamed shapes: the normalization of
 // launch_norm and the re-layout of launch_w_to_blocked in one pass.
 hipError_t launch_norm_blocked(const Problem &p, const void *wt, void *wb, hipStream_t s);
+int64_t wide_fwd_bytes(const Problem &p);
 hipError_t launch_fwd_wide(const Problem &p, hipStream_t s);
 hipError_t launch_fwd_wide_sum(const Problem &p, hipStream_t s);
 // Planes of any type and layout with both sides up to kLineSide (scan_line.hip).

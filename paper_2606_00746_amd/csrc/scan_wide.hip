@@ -1044,6 +1044,16 @@ hipError_t launch_fwd_wide_sum(const Problem &p, hipStream_t st)
                          : fwd_wide_sum_t<4, 0, 0>(p, st);
 }
 
+// Workspace of launch_fwd_wide.
+int64_t wide_fwd_bytes(const Problem &p)
+{
+    Workspace count;
+    count.counting = true;
+    Problem q = p;
+    q.ws = &count;
+    return launch_fwd_wide(q, nullptr) == hipSuccess ? (int64_t)count.used : INT64_MAX / 2;
+}
+
 hipError_t launch_fwd_wide(const Problem &p, hipStream_t st)
 {
     const int D = __builtin_popcount(p.mask);

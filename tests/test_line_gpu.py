@@ -90,6 +90,35 @@ def test_caller_with_less_workspace():
         assert torch.equal(a.view(torch.int16), b.view(torch.int16)), k
 
 
+@pytest.mark.parametrize("wl,same", [
+    (case("less-forward-wide", 1, 8, 8, 128, 128), False),   # rounds of a plane: general
+    (case("less-forward-cpg64", 3, 64, 1, 72, 80), True),    # rounds of a group
+    (case("less-forward-odd", 1, 8, 4, 77, 101), False),
+], ids=lambda v: getattr(v, "name", ""))
+def test_forward_with_less_workspace(wl, same):
+    """A forward whose caller has what the general family takes (and no less) is
+    accepted, whichever family the query sizes."""
+    torch = require_gpu()
+    print(f"[case] {wl.name}", flush=True)
+    inputs = gi.make_inputs(wl)
+    t = upload(inputs, wl.dtype, wl.dirs)
+    ref = gspn.scan_fwd(t["x"], t["w"], t["lam"], t["u"], wl.dirs)
+    less = 4 * 4 * wl.B * wl.C * wl.H * wl.W
+    assert gspn.workspace_size(gspn.OP_FWD, t["x"], t["w"], wl.dirs) > less
+    y = torch.full_like(t["x"], float("nan"))
+    ws = torch.empty(less, dtype=torch.uint8, device="cuda")
+    args = [t[k].data_ptr() for k in ("x", "w", "lam", "u")] + [y.data_ptr(), wl.dirs, wl.B, wl.C,
+                                                              wl.G, wl.H, wl.W, gspn.BF16,
+                                                              ws.data_ptr()]
+    stream = torch.cuda.current_stream().cuda_stream
+    assert gspn.gspn_scan_fwd(*args, less - 1, stream) == -9
+    assert gspn.gspn_scan_fwd(*args, less, stream) == 0
+    torch.cuda.synchronize()
+    if same:
+        assert torch.equal(y.view(torch.int16), ref.view(torch.int16))
+    check_against_oracle(inputs, {"y": to_host(y)}, wl, False, wl.name)
+
+
 def test_line_rounds():
     """More planes than one round's workspace (512 MB) holds: units of the
     first, a middle and the last round against the oracle."""
