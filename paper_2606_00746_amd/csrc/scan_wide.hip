@@ -15,21 +15,20 @@
 // Where the plane's fp32 sum fits in LDS beside x (sides up to about 160, blocked
 // tensors), the directions add to it there (fwd_wide_sum_kernel; this also takes
 // sides below 65 that no square family has).  A 256 x 256 sum does not fit, so
-// there each direction writes u_d * h_d to an fp32 plane in its own line-major order (whole lines per
-// store) and a tiled kernel sums the directions in direction-bit order,
-// transposing the horizontal ones through LDS, and stores y once.  The scan
-// and the sum alternate in rounds of planes, so that the sum finds much of
-// its round's planes still in the Infinity Cache (wide_round).
+// there each direction writes u_d * h_d to an fp32 plane in its own line-major
+// order (whole lines per store) and a tiled kernel sums the directions in
+// direction-bit order, transposing the horizontal ones through LDS, and stores
+// y once.  The scan and the sum alternate in rounds of planes, so that the sum
+// finds much of its round's planes still in the Infinity Cache (wide_round).
 //
-// Pixel-major per-direction tensors are first copied into the blocked order
-// of their direction in the caller's workspace (pieces_kernel: whole rows in
-// through LDS, whole 8-line blocks out), and the scan then runs as on blocked
-// tensors.  Read in place, a vertical scan would take 2 bytes of a row per
-// lane and load (8 loads per 16-byte piece, 40 per block of 8 lines and
-// position group), a horizontal one 16 bytes from each of 64 rows; the copy
-// costs one read and one write of lam, u and w at full bandwidth instead.
+// Pixel-major tensors of the horizontal directions are first copied into the
+// blocked order in the caller's workspace (pieces_kernel: whole rows in through
+// LDS, whole 8-line blocks out), and their scans then run as on blocked tensors:
+// read in place they would take 16 bytes from each of 64 rows.  The vertical
+// directions are read in place, whole rows (wide_vert_pm).  Few planes, and lines
+// of at most 128, are the line family's in that layout (line_fwd_preferred).
 //
-// With few channel planes the same direction pass runs on chunks of the scan
+// With few blocked channel planes the same direction pass runs on chunks of the scan
 // (fwd_wide_chunk_kernel, wide_carry_kernel): end states from zero, carries
 // through w alone, then every chunk again from its carry; wide_chunks picks
 // the chunk count from the shape.
@@ -1060,7 +1059,8 @@ hipError_t launch_fwd_wide(const Problem &p, hipStream_t st)
     const int64_t n = (int64_t)p.B * p.C * p.H * p.W;
     const size_t lds = wide_lds_bytes(p.H, p.W);
     const int64_t fit = wide_fit(lds);     // one device query per call
-    const int K = wide_chunks(p, fit);
+    // (pixel-major calls of so few planes are the line family's)
+    const int K = p.layout == kPixelMajor ? 1 : wide_chunks(p, fit);
     // fp32 direction planes, then (chunked) the chunk states
     const int64_t nst = K > 1 ? (int64_t)p.B * p.C * D * K * std::max(p.H, p.W) : 0;
     float *ys = nullptr;
@@ -1086,51 +1086,41 @@ hipError_t launch_fwd_wide(const Problem &p, hipStream_t st)
         if (K == 1)
             return rounds(p, nullptr);
         e = fwd_wide_l(p, st, ys, ys + D * n, lds, K, 0, planes);
-    } else {
-        // Blocked copies (workspace) of lam, u and w, then the blocked scan.
-        // The single pass reads the vertical directions in place (whole rows,
-        // wide_vert_pm), so only the horizontal ones are copied; the chunked
-        // passes take every direction from copies.
-        const int nv = __builtin_popcount(p.mask & 3), nh = D - nv;
-        const int nc = K > 1 ? D : nh;                    // directions copied
-        const int64_t bc = (int64_t)p.B * p.C, bg3 = (int64_t)p.B * p.G * 3;
-        const int64_t HW = (int64_t)p.H * p.W;
-        void *cl = nullptr, *cu = nullptr, *cw = nullptr;
-        if (nc > 0) {
-            e = p.ws->take(&cl, (size_t)(nc * bc * HW) * 2);
-            if (e == hipSuccess)
-                e = p.ws->take(&cu, (size_t)(nc * bc * HW) * 2);
-            if (e == hipSuccess)
-                e = p.ws->take(&cw, (size_t)(nc * bg3 * HW) * 2);
-        }
-        if (e != hipSuccess || p.ws->counting)
-            return e;
-        const int cv = nc - nh;                           // vertical directions copied
-        const int64_t skip = (int64_t)(nv - cv);          // vertical slots not copied
-        if (nc > 0) {
-            e = launch_pieces(static_cast<const bf16_t *>(p.lam) + skip * bc * HW, cl, cv * bc,
-                              nh * bc, p.H, p.W, st);
-            if (e == hipSuccess)
-                e = launch_pieces(static_cast<const bf16_t *>(p.u) + skip * bc * HW, cu, cv * bc,
-                                  nh * bc, p.H, p.W, st);
-            if (e == hipSuccess)
-                e = launch_pieces(static_cast<const bf16_t *>(p.w) + skip * bg3 * HW, cw,
-                                  cv * bg3, nh * bg3, p.H, p.W, st);
-            if (e != hipSuccess)
-                return e;
-        }
-        Problem q = p;
-        q.lam = cl;
-        q.u = cu;
-        q.w = cw;
-        q.layout = kBlocked;
-        if (K == 1)
-            return rounds(q, &p);
-        e = fwd_wide_l(q, st, ys, ys + D * n, lds, K, 0, planes);
+        return e == hipSuccess ? launch_sum_wide(p, ys, st, 0, planes) : e;
     }
-    if (e == hipSuccess)
-        e = launch_sum_wide(p, ys, st, 0, planes);
-    return e;
+    // Blocked copies (workspace) of the horizontal directions' lam, u and w; the
+    // vertical ones are read in place (whole rows, wide_vert_pm).
+    const int nv = __builtin_popcount(p.mask & 3), nh = D - nv;
+    const int64_t bc = (int64_t)p.B * p.C, bg3 = (int64_t)p.B * p.G * 3;
+    const int64_t HW = (int64_t)p.H * p.W;
+    void *cl = nullptr, *cu = nullptr, *cw = nullptr;
+    if (nh > 0) {
+        e = p.ws->take(&cl, (size_t)(nh * bc * HW) * 2);
+        if (e == hipSuccess)
+            e = p.ws->take(&cu, (size_t)(nh * bc * HW) * 2);
+        if (e == hipSuccess)
+            e = p.ws->take(&cw, (size_t)(nh * bg3 * HW) * 2);
+    }
+    if (e != hipSuccess || p.ws->counting)
+        return e;
+    if (nh > 0) {
+        e = launch_pieces(static_cast<const bf16_t *>(p.lam) + nv * bc * HW, cl, 0, nh * bc, p.H,
+                          p.W, st);
+        if (e == hipSuccess)
+            e = launch_pieces(static_cast<const bf16_t *>(p.u) + nv * bc * HW, cu, 0, nh * bc, p.H,
+                              p.W, st);
+        if (e == hipSuccess)
+            e = launch_pieces(static_cast<const bf16_t *>(p.w) + nv * bg3 * HW, cw, 0, nh * bg3,
+                              p.H, p.W, st);
+        if (e != hipSuccess)
+            return e;
+    }
+    Problem q = p;
+    q.lam = cl;
+    q.u = cu;
+    q.w = cw;
+    q.layout = kBlocked;
+    return rounds(q, &p);
 }
 
 }  // namespace gspn
