@@ -44,6 +44,10 @@ CASES = [
     ("wide-72x136", case("wide-72x136", 1, 4, 2, 72, 136), "pixel"),
     ("chunked-256x256-fwd", case("chunked-256x256", 1, 8, 2, 256, 256, backward=False), "pixel"),
     ("general-70x100", case("general-70x100", 1, 4, 2, 70, 100), "pixel"),
+    ("plane-37x37", case("plane-37x37", 2, 144, 12, 37, 37), "pixel"),
+    ("line-72x101", case("line-72x101", 1, 36, 3, 72, 101), "pixel"),
+    ("sum-40x72-blocked", case("sum-40x72", 2, 8, 4, 40, 72, backward=False), "blocked"),
+    ("wide-136x144", case("wide-136x144", 1, 132, 6, 136, 144, backward=False), "pixel"),
 ]
 
 
