@@ -9,14 +9,18 @@ HERE = os.path.join(ROOT, "tests", "host")
 CSRC = os.path.join(ROOT, "paper_2606_00746_amd", "csrc")
 
 
-def _build_and_run(tmp_path, name, *link):
+LIB = os.path.join(ROOT, "paper_2606_00746_amd", "libgspn.so")
+LINK = (LIB, "-Wl,-rpath," + os.path.dirname(LIB))
+
+
+def _build_and_run(tmp_path, name, *link, stdin=""):
     from paper_2606_00746_amd import build as lib_build
     exe = str(tmp_path / name)
     cmd = [lib_build.hipcc(), "--offload-arch=" + lib_build.ARCH, "--offload-host-only", "-O2",
            "-std=c++17", "-Wall", "-I", CSRC, "-I", os.path.join(ROOT, "include"), "-x", "hip",
            os.path.join(HERE, name + ".cpp"), "-x", "none", *link, "-o", exe]
     for c in (cmd, [exe]):
-        r = subprocess.run(c, capture_output=True, text=True, timeout=600)
+        r = subprocess.run(c, input=stdin, capture_output=True, text=True, timeout=600)
         assert r.returncode == 0, f"{' '.join(c)}\n{r.stdout[-4000:]}\n{r.stderr[-4000:]}"
     return r.stdout
 
@@ -26,9 +30,31 @@ def test_plane_records_stay_inside_lds(tmp_path):
 
 
 def test_routes_follow_the_measured_times(tmp_path):
-    assert "all routes clean" in _build_and_run(tmp_path, "routes", os.path.join(
-        ROOT, "paper_2606_00746_amd", "libgspn.so"),
-        "-Wl,-rpath," + os.path.join(ROOT, "paper_2606_00746_amd"))
+    assert "all routes clean" in _build_and_run(tmp_path, "routes", *LINK)
+
+
+def test_gpu_cases_take_the_family_they_name(tmp_path):
+    """The cases of the GPU tests that stand for one kernel family are that
+    family's, pass by pass and layout by layout."""
+    import test_line_gpu
+    import test_plane_gpu
+    import test_wide_sum_gpu
+    both = ("fwd", "bwd", "fwd_blocked", "bwd_blocked")
+    want = {}
+    for cases, family, ops in ((test_plane_gpu.PLANE, "plane", both),
+                               (test_plane_gpu.SMALL, "small", both),
+                               (test_line_gpu.CASES, "line", both),
+                               (test_wide_sum_gpu.WIDE, "wide", ("fwd",)),
+                               (test_wide_sum_gpu.CASES, "sum", ("fwd_blocked",))):
+        for wl in cases:
+            head = wl.name.split("-")[0]
+            for op in ops:
+                want[wl, op] = {"general": "general", "planes": "wide"}.get(head, family)
+    lines = [f"{wl.name} {wl.B} {wl.C} {wl.G} {wl.H} {wl.W} {int(wl.dtype == 'bf16')} {wl.dirs} {op}"
+             for wl, op in want]
+    out = _build_and_run(tmp_path, "family", *LINK, stdin="\n".join(lines) + "\n")
+    got = [tuple(ln.split()) for ln in out.splitlines()]
+    assert got == [(wl.name, op, family) for (wl, op), family in want.items()]
 
 
 def test_line_family_sizes_its_own_workspace():

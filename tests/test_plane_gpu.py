@@ -4,7 +4,8 @@ blocks and lanes per channel (16, 17, 32, 33, 40 and 41 a side), odd and even
 widths (odd planes start at any 2-byte address), one pixel, rows and columns,
 one channel per group, channels that fill a workgroup unevenly, a group in
 several workgroups, both types and layouts; shapes with enough planes for the
-plane family and, with few, for the line family and the small forward."""
+plane family in every pass and, with few, for the line family and the small
+kernels."""
 import numpy as np
 import pytest
 
@@ -42,15 +43,52 @@ CASES = [
 ]
 
 
+# planes enough that the plane family takes both passes in both layouts: every
+# count of 8-step blocks, both types
+PLANE = [
+    case("7x7-cpg33-all", 16, 231, 7, 7, 7),
+    case("8x7-f32-cpg9", 8, 450, 50, 8, 7, dtype="f32", gate="normal"),
+    case("13x14-cpg3-dirs11", 8, 402, 134, 13, 14, dirs=11),
+    case("16x9-cpg10-dirs6", 8, 400, 40, 16, 9, dirs=6),
+    case("15x16-f32-cpg9-all", 8, 405, 45, 15, 16, dtype="f32", gate="normal"),
+    case("17x17-cpg13-all", 8, 221, 17, 17, 17),
+    case("24x20-f32-cpg12", 6, 288, 24, 24, 20, dtype="f32", gate="normal"),
+    case("20x17-f32-B2T", 4, 2048, 256, 20, 17, dirs=2, dtype="f32", gate="normal"),
+    case("28x28-cpg12-all", 8, 216, 18, 28, 28),
+    case("25x31-cpg5-dirs3", 8, 250, 50, 25, 31, dirs=3),
+    case("18x28-f32-cpg6-dirs13", 6, 300, 50, 18, 28, dirs=13, dtype="f32", gate="normal"),
+    case("37x37-cpg32-all", 4, 256, 8, 37, 37),
+    case("40x21-cpg8", 4, 256, 32, 40, 21),
+    case("33x34-f32-cpg4-dirs12", 4, 256, 64, 33, 34, dirs=12, dtype="f32", gate="normal"),
+    case("36x11-f32-cpg8", 4, 256, 32, 36, 11, dtype="f32", gate="normal"),
+    case("48x19-cpg12-dirs12", 4, 252, 21, 48, 19, dirs=12),
+    case("41x15-f32-cpg8", 4, 256, 32, 41, 15, dtype="f32", gate="normal"),
+    case("53x20-cpg8", 4, 256, 32, 53, 20),
+    case("10x55-f32-cpg8", 4, 256, 32, 10, 55, dtype="f32", gate="normal"),
+    case("64x12-cpg9", 4, 252, 28, 64, 12),
+    case("9x61-f32-cpg8", 4, 256, 32, 9, 61, dtype="f32", gate="normal"),
+]
+
+# planes of a few pixels, which the small kernels take in both passes
+SMALL = [
+    case("2x2-f32-cpg3", 2, 6, 2, 2, 2, dtype="f32", gate="normal"),
+    case("3x3-cpg4-dirs7", 3, 8, 2, 3, 3, dirs=7),
+    case("1x3-cpg16", 1, 32, 2, 1, 3),
+    case("1x13-G=C-R2L", 2, 5, 5, 1, 13, dirs=8),
+]
+
+
 @pytest.mark.parametrize("layout", ["pixel", "blocked"])
-@pytest.mark.parametrize("wl", CASES, ids=lambda w: w.name)
+@pytest.mark.parametrize("wl", CASES + PLANE + SMALL, ids=lambda w: w.name)
 def test_plane_parity(wl, layout):
     inputs = gi.make_inputs(wl, with_dy=True)
     got = run_gpu(inputs, wl, True, layout=layout)
     check_against_oracle(inputs, got, wl, True, f"{wl.name} {layout}")
 
 
-@pytest.mark.parametrize("wl", [case("nan-28x28", 4, 192, 16, 28, 28),
+@pytest.mark.parametrize("wl", [case("nan-13x14", 8, 402, 134, 13, 14),
+                                case("nan-40x21", 4, 256, 32, 40, 21),
+                                case("nan-28x28", 4, 192, 16, 28, 28),
                                 case("nan-37x37", 2, 288, 144, 37, 37),
                                 case("nan-few-45x64", 1, 4, 2, 45, 64)], ids=lambda w: w.name)
 def test_ignored_taps_may_hold_nan(wl):
@@ -64,7 +102,9 @@ def test_ignored_taps_may_hold_nan(wl):
         assert np.array_equal(got[k], clean[k]), k
 
 
-@pytest.mark.parametrize("wl", [case("inf-16x16-f32", 4, 192, 16, 16, 16, dtype="f32"),
+@pytest.mark.parametrize("wl", [case("inf-13x15-cpg12", 8, 408, 34, 13, 15),
+                                case("inf-40x21", 4, 256, 32, 40, 21),
+                                case("inf-16x16-f32", 4, 192, 16, 16, 16, dtype="f32"),
                                 case("inf-13x15", 4, 192, 16, 13, 15),
                                 case("inf-37x37", 2, 288, 144, 37, 37),
                                 case("inf-few-64x40", 1, 8, 2, 64, 40),
