@@ -67,10 +67,16 @@
  * takes for its sizes; the call takes `workspace` (16-byte aligned, not
  * overlapping any other buffer of the call; may be NULL when the size is 0)
  * and its size `workspace_bytes`, and returns GSPN_ERR_WORKSPACE when it is
- * smaller than needed.  Planes above 64 take the size given for their fastest
- * plan and run with less too, in smaller parts (the same results bit for bit)
- * or, below what a part takes, on slower kernels.  The workspace's contents on entry do not matter and
- * are undefined after the call; calls that share a workspace must not run
+ * smaller than needed.  Planes up to 256 a side outside the square kernels keep
+ * fp32 lines and turned copies there: their size may be several times that of
+ * the tensors, up to 512 MB, or one weight group's where that is more.  They run
+ * with less too, in smaller parts (the same results bit for bit) or on kernels
+ * that need less: above 64 a side the fp32 planes of gspn_scan_fwd's directions
+ * or the backward's partial sums, up to 64 a side nothing or the latter (their
+ * results agree within the rounding of fp32).  What the kernels that need the
+ * least take is accepted, and the query gives no more where that is below 704 KB.
+ * The workspace's contents on entry do not matter and are undefined after the
+ * call; calls that share a workspace must not run
  * concurrently.
  *
  * Errors: every argument check runs on the host before any HIP call, so an
@@ -127,7 +133,7 @@ extern "C" {
 
 /*
  * Bytes of workspace that operation `op` (GSPN_OP_*) takes for these sizes,
- * in *bytes (0 for most shapes).  The same argument checks as the call; the
+ * in *bytes (0 for many shapes).  The same argument checks as the call; the
  * plan of a call is the same for every call with these sizes and at least
  * this workspace on one device.
  * Needs the current device (GSPN_ERR_HIP without one).
@@ -283,8 +289,9 @@ int gspn_scan_bwd_norm_reserve(const void *x, const void *w_logits, const void *
  * and errors as gspn_scan_bwd; its workspace is a fixed device array of
  * GSPN_STATIC_SCRATCH_BYTES that the library holds on every GPU it runs on
  * until the process ends (looked up, not allocated, at the first call on a
- * device).  Returns GSPN_ERR_WORKSPACE, before any launch, when the call
- * needs more (gspn_workspace_size with GSPN_OP_BWD gives the need).  Every
+ * device).  A call whose size (gspn_workspace_size with GSPN_OP_BWD) is larger
+ * runs as gspn_scan_bwd does with a workspace of that many bytes; returns
+ * GSPN_ERR_WORKSPACE, before any launch, where that is refused.  Every
  * call on one GPU shares that GPU's array: calls that overlap in time on one
  * GPU (concurrent streams or threads) race and must not be issued; calls
  * ordered on one stream are safe.  Allocates nothing, not even through

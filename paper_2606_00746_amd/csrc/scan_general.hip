@@ -1,5 +1,7 @@
 // Line scans for planes with a side above 256 (up to GSPN_MAX_SIDE), and for
-// callers whose workspace holds no round of scan_line.hip.
+// those above 64 whose workspace (the query's, where that is small, or a caller's)
+// holds no round of scan_line.hip that is worth its launches, and blocked forwards
+// of a few steps.
 //
 // A workgroup runs one line scan; each thread owns positions j, j + NT, ...
 // of the line and the previous line's states are read from a triple-buffered
