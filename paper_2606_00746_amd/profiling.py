@@ -46,10 +46,17 @@ _FAMILY_SOURCES = (("_med_", _MED), ("dw_sum", _MED), ("_pm_", ("scan_pm.hip",))
                    ("to_blocked", ("scan_pm.hip",)), ("_wide_", ("scan_wide.hip",)),
                    ("pieces_kernel", ("scan_wide.hip",)), ("_tiny_", ("scan_tiny.hip",)),
                    ("_small_", ("scan_small.hip",)), ("_general_", ("scan_general.hip",)),
+                   ("plane_", ("scan_plane.hip", "plane_lds.hpp")),
+                   *((k, ("scan_line.hip",)) for k in ("sweep_kernel", "grad_kernel",
+                                                       "merge_kernel", "transpose_kernel",
+                                                       "rows_kernel", "dw_parts_kernel")),
+                   *((k, ("latent.hip",)) for k in ("proj_", "params_blocks", "zero_margin")),
                    ("norm", ("scan_norm.hip",)))
-# kernels that run at the start of a call (re-layouts into the blocked order):
-# they belong to the call whose scan kernel follows them
-_PREPASS = ("to_blocked_kernel", "norm_to_blocked_kernel", "pieces_kernel")
+# kernels that run at the start of a call (re-layouts into the blocked order or
+# into rows, and the line family's sweeps): they belong to the call whose scan
+# kernel follows them
+_PREPASS = ("to_blocked_kernel", "norm_to_blocked_kernel", "pieces_kernel", "transpose_kernel",
+            "rows_kernel", "sweep_kernel")
 # the normalization kernels of the _norm calls: forming the weights at the
 # start of a call, or the logits' gradient at the end of a backward
 _NORM = ("norm_kernel", "norm_pm_kernel")
@@ -96,11 +103,18 @@ def short_name(name: str) -> str:
 def call_of(kernel: str) -> str | None:
     """Which library call a kernel belongs to ('fwd' or 'bwd'), None for others."""
     k = short_name(kernel)
-    if k.startswith(("fwd_", "sum_")):
+    if k.startswith(("fwd_", "sum_", "merge_kernel")):
         return "fwd"
-    if k.startswith(("bwd_", "dw_sum", "dw_reduce", "cast_")):
+    if k.startswith(("bwd_", "dw_sum", "dw_reduce", "dw_parts", "grad_kernel", "plane_dw", "cast_")):
         return "bwd"
+    if k.startswith("plane_kernel"):                    # <blocks, type, backward, batch>
+        return "bwd" if k.split(",")[2].strip() == "true" else "fwd"
     return None
+
+
+def _library(kernel: str) -> bool:
+    k = short_name(kernel)
+    return call_of(k) is not None or k.startswith(_PREPASS) or k.startswith(_NORM)
 
 
 def trace_summary(db: str, out: str, command: str) -> str:
@@ -148,18 +162,15 @@ def _calls_in_order(disp: list) -> list:
     and one after the run's last scan kernel to that kernel's call (the
     transpose of a weight gradient, the logits' gradient at the end of a
     backward)."""
-    def library(k):
-        return call_of(k) is not None or k.startswith(_PREPASS) or k.startswith(_NORM)
-
     names = [short_name(k) for k, _ in disp]
     out = [None] * len(disp)
     n = 0
     while n < len(names):
-        if not library(names[n]):
+        if not _library(names[n]):
             n += 1
             continue
         m = n
-        while m < len(names) and library(names[m]):
+        while m < len(names) and _library(names[m]):
             m += 1
         nxt = None
         for i in range(m - 1, n - 1, -1):
@@ -247,7 +258,7 @@ def waves_summary(csv_path: str, out: str, command: str) -> str:
              f"{'kernel':<44} {'disp':>4} {'wave_cyc':>12} {'wait':>6} {'iss_wt':>6} "
              f"{'busy':>6} {'valu':>6} {'vmem':>6} {'lds':>6}"]
     for k, cv in vals.items():
-        if call_of(k) is None:
+        if not _library(k):
             continue
         m = {c: sum(v) / len(v) for c, v in cv.items()}
         wc = m.get("SQ_WAVE_CYCLES", 0.0)

@@ -164,3 +164,27 @@ def test_kernels_after_the_last_scan_belong_to_its_call(tmp_path):
     assert rec["kernels"]["pieces_kernel [bwd]"]["dispatches_per_call"] == 1
     assert rec["bytes_per_call"]["fwd"] == (2 * 103 + 103) * 1024
     assert rec["bytes_per_call"]["bwd"] == (2 * 320 + 320) * 1024
+
+
+def test_line_and_plane_kernels_belong_to_their_calls(tmp_path):
+    # the line family: turned rows and sweeps of either call, then the merge or
+    # the gradients; the plane family: one kernel whose template names the pass
+    copy = "__amd_rocclr_copyBuffer(char const*, char*)"
+    ns = "void gspn::(anonymous namespace)::"
+    turn, sweep = ns + "transpose_kernel<unsigned short>(int)", ns + "sweep_kernel<unsigned short, 2, false>(int)"
+    merge, grad = ns + "merge_kernel<unsigned short, true>(int)", ns + "grad_kernel<unsigned short, true>(int)"
+    parts = ns + "dw_parts_kernel<unsigned short>(int)"
+    fwd, bwd = (ns + f"plane_kernel<5, unsigned short, {b}, 4>(int)" for b in ("false", "true"))
+    flush = "void at::native::reduce_kernel<512, 1>(int)"
+    step = [(flush, 999.0), (turn, 1.0), (sweep, 10.0), (merge, 100.0), (flush, 999.0), (turn, 2.0),
+            (sweep, 20.0), (grad, 200.0), (parts, 3.0), (flush, 999.0), (fwd, 1000.0),
+            (flush, 999.0), (bwd, 2000.0)]
+    _csv(tmp_path / "f.csv", "FETCH_SIZE", [(copy, 4096.0)] + step)
+    _csv(tmp_path / "w.csv", "WRITE_SIZE", [(copy, 4096.0)] + step)
+    rec = profiling.traffic_record(str(tmp_path / "f.csv"), str(tmp_path / "w.csv"), "wl", 4, "cmd",
+                                   calls=1)
+    assert rec["bytes_per_call"]["fwd"] == 2 * (111 + 1000) * 1024
+    assert rec["bytes_per_call"]["bwd"] == 2 * (225 + 2000) * 1024
+    for f in ("scan_line.hip", "scan_plane.hip", "plane_lds.hpp"):
+        assert f in rec["source_files"]
+    assert "scan_med.hip" not in rec["source_files"]
