@@ -751,7 +751,12 @@ int plane_channels(const Problem &p, bool bwd)
 //    222 / 467 and 265 / 905; fp32 40 x 56, 2 channels: 116 / 219 and 39 / 124.
 //    A pixel-major forward with vertical directions, which line need not turn
 //    around, is line's up to 6: 51 x 33, T2B and B2T, G = C, 1468 planes: 68 and
-//    29; 41 x 41, four directions, G = C, 1216: 120 and 61; with those alone, in
+//    29; 41 x 41, four directions, G = C, 1216: 120 and 61; but not with shared
+//    taps and many planes, where only the waves in flight count: four directions,
+//    bf16 47 x 47, 30 a group, 8460: 310 and 384 (44 x 44, 8 a group, 2944: 112 and
+//    101), fp32 41 x 41, 32 a group, 3072: 122 and 149, nor one direction in a
+//    single round of workgroups: 45 x 45 T2B, 1024 in 256: 13 and 17 (42 x 40, 1056
+//    in 264: 21 and 17); with vertical ones alone up to 32 a side, in
 //    waves of two channels, up to 8: 31 x 31, 3 a group, 4020: 52 and 36; in
 //    fp32 up to 10, until some 8000 channels: 24 x 24, 1632: 27 and 18;
 //  * with few workgroups it is one workgroup's time, where the line family
@@ -781,7 +786,10 @@ bool plane_preferred(const Problem &p, bool bwd)
     }
     const bool horizontal = (p.mask & 3) == 0;
     const bool one = p.layout == kPixelMajor && horizontal && p.mask != 12;
-    return per_cu * q.nwaves >= (horizontal || p.layout != kPixelMajor ? 4 : 6) &&
+    const int D = __builtin_popcount(p.mask);
+    const bool shared = (D > 2 && p.C / p.G >= 4 && (int64_t)p.B * p.C >= (p.dtype == 0 ? 3000 : 3600)) ||
+                        (D == 1 && wgs <= 256);
+    return per_cu * q.nwaves >= (horizontal || p.layout != kPixelMajor || shared ? 4 : 6) &&
            wgs >= (one ? 28 : 128) && (horizontal || wgs * q.nwaves >= 600);
 }
 

@@ -408,7 +408,11 @@ int lanes_per_line(int H, int W)
 //    four channels are of one group: 13 x 13, four directions, G = C, w = 1024:
 //    18 / 25 / 96; 4 channels a group, w = 512: 11 / 13 / 43, 1024: 18 / 14 / 71; 2
 //    channels, w = 700: 14 / 14, 1100: 20 / 16; 15 x 15 blocked, 2, w = 5309: 84 /
-//    117;
+//    117.  At G = C its loads of horizontal lines, 16 to a wave, stop being served
+//    by the cache with many planes in flight (`many`): fp32 8 x 8 blocked, three
+//    directions, w = 4920: 73 / 46, 10 x 10, four, 19710: 417 / 286; bf16 11 x 11,
+//    four, 7104 and less: even, 28072: 423 / 316, but with rows of 16 bytes 9 x 8,
+//    12632: 106 / 133, and blocked 9 x 9, 35073: 453 / 486;
 //  * pixel-major with horizontal directions: few planes up to 40 a side, 28 x 28
 //    bf16, B*C = 256: 14 / 27 / 16, 1024: 23 / 27 / 29, 12288: 208 / 87 / 249; fp32
 //    1024: 39 / 31 / 28; 37 x 37 bf16 256: 20 / 27 / 21, 1024: 73 / 28 / 38.  One
@@ -427,7 +431,10 @@ int lanes_per_line(int H, int W)
 //  * blocked up to 64, where line turns every plane around first: bf16 53 x 53,
 //    three directions, w = 224: 22 / 71 / 53; 47 x 47, four, w = 2112: 134 / 161 /
 //    131; planes that plane holds 6 or 8 of until w = 800 (44 x 28 L2R, 828: 24 /
-//    15 / 27).  fp32, whose planes are twice the bytes to turn, until one or two
+//    15 / 27), large ones until 4000 (36 x 55, two directions, 1920: 76 / 74 / 69,
+//    44 x 44, two, 6656: 243 / 189 / 194); of three or four directions 6 suffice
+//    from 2400 with taps to share (33 x 42, four, 3 a group, 3072: 155 / 122 / 191,
+//    38 x 38, 12 a group, 2016: 107 / 113 / 109).  fp32, whose planes are twice the bytes to turn, until one or two
 //    directions are 1400 waves and more 2200 (55 x 55, four, w = 216: 42 / 140 / 68;
 //    48 x 33, three, w = 1576: 118 / 182 / 165), but for large planes of several
 //    channels a group (64 x 64, four, 12 a group, w = 36: 52 / 130 / 39) or of few
@@ -441,8 +448,11 @@ bool small_fwd_preferred(const Problem &p)
     const bool gather = pm && (p.mask & 12) != 0;
     if (w > kMaxThreads / 256)
         return false;
-    if (T == 16)
-        return cpg == 1 || w < 800 || (!pm && cpg < 4 && HW >= 190);
+    if (T == 16) {
+        const bool many = (p.mask & 12) != 0 && HW >= 40 && HW <= (f32 && !pm ? 100 : 180) &&
+                          (f32 ? w >= 4900 : pm && p.W % 8 != 0 && w >= 12000);
+        return w < 800 || (cpg == 1 ? !many : !pm && cpg < 4 && HW >= 190);
+    }
     if (gather) {
         if (T == 64 && D == 1)
             return w <= (f32 ? 128 : 256);
@@ -460,7 +470,8 @@ bool small_fwd_preferred(const Problem &p)
         return p.H <= 40 && p.W <= 40 && w * (f32 ? 4 : 2) <= 512;
     if (f32)
         return w * D < (D > 2 ? 2200 : 1400) && (D <= 2 || HW < 2400 || (cpg == 1 && w >= 100));
-    return w < 800 || HW >= 1800 || plane_channels(p, false) < (D > 2 ? 8 : 6);
+    return w < 800 || (HW >= 1800 && w < 4000) ||
+           plane_channels(p, false) < (D > 2 && (w < 2400 || cpg < 3) ? 8 : 6);
 }
 
 // ... and the backward: planes of a few pixels, which plane's staging and
