@@ -77,7 +77,20 @@ static const Call calls[] = {
     {false, true, 57, 59, 1, 4, 1, 0, 4, {14.7f, 32.8f, 19.4f}},
     {false, true, 21, 38, 8, 128, 4, 1, 7, {41.8f, 25.5f, 44.3f}},
     {false, true, 41, 41, 7, 3, 1, 1, 7, {17.2f, 35.2f, 29.9f}},
-    {false, true, 32, 43, 1, 64, 2, 1, 15, {21.9f, 46.6f, 36.6f}},
+    {false, true, 32, 43, 1, 64, 2, 1, 15, {21.9f, 46.6f, 36.6f}},    // many planes
+    {false, false, 10, 10, 2, 39420, 39420, 0, 15, {416.7f, 286.4f, 1729.4f}},
+    {false, true, 8, 8, 8, 2460, 2460, 0, 7, {72.5f, 46.0f, 170.2f}},
+    {false, false, 11, 11, 16, 10128, 10128, 1, 15, {625.6f, 455.3f, 3687.0f}},
+    {false, false, 9, 8, 4, 12632, 12632, 1, 15, {106.0f, 133.0f, 1030.0f}},
+    {false, true, 9, 9, 8, 17536, 17536, 1, 15, {453.0f, 486.0f, 1864.0f}},
+    {false, false, 47, 47, 1, 8460, 282, 1, 15, {1008.3f, 309.7f, 384.3f}},
+    {false, false, 44, 44, 32, 92, 11, 1, 15, {288.0f, 112.0f, 101.0f}},
+    {false, false, 41, 41, 32, 96, 3, 0, 15, {396.5f, 122.2f, 149.1f}},
+    {false, false, 45, 45, 16, 64, 8, 1, 1, {29.1f, 12.5f, 16.6f}},
+    {false, false, 42, 40, 4, 264, 66, 1, 1, {25.0f, 21.0f, 17.0f}},
+    {false, true, 38, 38, 4, 2178, 363, 1, 7, {319.6f, 264.5f, 374.0f}},
+    {false, true, 26, 35, 2, 1953, 279, 1, 15, {180.3f, 120.8f, 135.7f}},
+    {false, true, 44, 44, 8, 832, 26, 1, 12, {242.6f, 188.9f, 193.6f}},
 };
 
 // Planes above 64 a side: line family in rounds of what the query's workspace holds /

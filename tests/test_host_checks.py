@@ -43,6 +43,7 @@ def test_gpu_cases_take_the_family_they_name(tmp_path):
     want = {}
     for cases, family, ops in ((test_plane_gpu.PLANE, "plane", both),
                                (test_plane_gpu.SMALL, "small", both),
+                               (test_plane_gpu.MANY, "plane", ("fwd",)),
                                (test_line_gpu.CASES, "line", both),
                                (test_wide_sum_gpu.WIDE, "wide", ("fwd",)),
                                (test_wide_sum_gpu.CASES, "sum", ("fwd_blocked",))):

@@ -77,6 +77,21 @@ SMALL = [
     case("1x13-G=C-R2L", 2, 5, 5, 1, 13, dirs=8),
 ]
 
+# one channel a group up to 16 a side: so many planes that the pixel-major forward is
+# the plane family's, with one channel in a wave of four
+MANY = [
+    case("many-8x8-f32-G=C", 10, 1960, 1960, 8, 8, dtype="f32", gate="normal"),
+    case("many-5x9-f32-G=C-dirs6", 10, 1961, 1961, 5, 9, dirs=6, dtype="f32", gate="normal"),
+    case("many-6x7-G=C-dirs12", 16, 3001, 3001, 6, 7, dirs=12),
+    case("many-4x11-G=C-dirs7", 16, 3000, 3000, 4, 11, dirs=7),
+]
+
+
+@pytest.mark.parametrize("wl", MANY, ids=lambda w: w.name)
+def test_many_planes_forward(wl):
+    inputs = gi.make_inputs(wl, with_dy=False)
+    check_against_oracle(inputs, run_gpu(inputs, wl, False), wl, False, wl.name)
+
 
 @pytest.mark.parametrize("layout", ["pixel", "blocked"])
 @pytest.mark.parametrize("wl", CASES + PLANE + SMALL, ids=lambda w: w.name)
