@@ -25,12 +25,12 @@
 // The work is taken in rounds of whole weight groups whose workspace fits in
 // kRoundBytes.
 //
-// 128 x 128, B = 2, C = 192, G = 6, four directions, bf16 (backward and the
-// wide family's forward): 13380 us with one workgroup per (direction, batch,
-// group), 381 us so.  Of that the sweeps take 83 us (they read and write 0.4
-// GB, 4.8 TB/s, bound by those bytes), the gradients 129 us (0.4 GB, 3 TB/s:
-// each of their phases waits for its tile, two workgroups a CU), the turned
-// copies 28 us.
+// 128 x 128, B = 2, C = 192, G = 6, four directions, bf16, training pair: 13315 us
+// with one workgroup per (direction, batch, group), 341 us so.  Of that the sweeps
+// take 48 us in the forward and 86 us in the backward (more than half of their wave
+// time waits to issue, three waves a SIMD), the gradients 131 us (474 MB, 3.6 TB/s:
+// each of their phases waits for its tile, two workgroups a CU), the turned copies
+// 16 and 29 us, the merge 26 us.
 #include <algorithm>
 
 #include "cdna.hpp"
@@ -1211,13 +1211,43 @@ hipError_t line_t(const Problem &p, bool bwd, hipStream_t st)
 
 }  // namespace
 
-// (Blocked forwards of a few steps are the launches that turn their planes into
-// rows: line / general, us: 12 x 118, T2B and B2T, B*C = 64: 17 / 11; 16 x 68, 19: 18 /
-// 14; 19 x 76, 32: 14 / 17.)
+// Blocked forwards that the general family does faster: its time is its steps, while
+// the line family's launches turn every plane into rows first, and of few channels a
+// group the taps as well (us, line / general):
+//  * up to 16 steps always: 12 x 118, T2B and B2T, B*C = 64: 17 / 11; 16 x 68, 19: 18 / 14;
+//  * both vertical directions: one or two channels a group until 44 steps, with few
+//    planes 34 (19 x 158, 995: 85 / 48; 40 x 122, 928: 126 / 79; 44 x 134, 124: 42 / 39, but
+//    44 x 90, 40: 25 / 31), more until 24 (20 x 132, 16 a group, 16: 20 / 18; 31 x 142, 4 a
+//    group, 48: 24 / 24);
+//  * one vertical direction, of one or two channels a group until 22 (22 x 121, 2 a
+//    group, 1676: 51 / 45; 24 x 77, 24: 16 / 19; 4 a group, 20 x 183, 560: 31 / 32), of one
+//    and 250 planes until 34 (27 x 158, 1120: 70 / 51; 34 x 73, 864: 50 / 48; 43 x 76, 736:
+//    48 / 55);
+//  * horizontal ones, whose lines of few positions the general family reads by lanes,
+//    only up to 350 planes: both until 24 steps, 36 of one or two channels a group and
+//    50 planes (169 x 23, 224: 45 / 30; 172 x 33, 100: 40 / 33; 126 x 33, 8: 25 / 33; 172 x
+//    30, 704: 108 / 188); one until 19 (102 x 17, 862: 39 / 29, but 82 x 27, fp32, 2592: 128
+//    / 265).
+static bool few_steps(const Problem &p)
+{
+    const bool vert = (p.mask & 12) == 0, horiz = (p.mask & 3) == 0;
+    const int steps = std::max((p.mask & 3) ? p.H : 0, (p.mask & 12) ? p.W : 0);
+    if (steps <= 16)
+        return true;
+    if ((p.H > p.W ? p.H : p.W) <= kSmallSide || !(vert || horiz))
+        return false;
+    const bool two = (p.mask & (p.mask - 1)) != 0;
+    const int64_t planes = (int64_t)p.B * p.C, cpg = p.C / p.G;
+    if (vert)
+        return two ? steps <= (cpg > 2 ? 24 : planes >= 50 ? 44 : 34)
+                   : cpg <= 2 && steps <= (cpg == 1 && planes >= 250 ? 34 : 22);
+    return two ? planes <= 350 && steps <= (cpg <= 2 && planes >= 50 ? 36 : 24)
+               : planes <= 900 && cpg <= 2 && steps <= 19;
+}
+
 bool line_supported(const Problem &p, bool bwd)
 {
-    const int steps = std::max((p.mask & 3) ? p.H : 0, (p.mask & 12) ? p.W : 0);
-    if (!bwd && p.layout != kPixelMajor && steps <= 16)
+    if (!bwd && p.layout != kPixelMajor && few_steps(p))
         return false;
     return (p.H > p.W ? p.H : p.W) <= kLineSide && line_plan(p, bwd).fits;
 }

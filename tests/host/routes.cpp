@@ -93,7 +93,7 @@ static const Call calls[] = {
     {false, true, 44, 44, 8, 832, 26, 1, 12, {242.6f, 188.9f, 193.6f}},
 };
 
-// Planes above 64 a side: line family in rounds of what the query's workspace holds /
+// Planes above 64 a side: line family, in rounds of what the query's workspace holds, /
 // general family.
 struct LongCall {
     bool bwd, blocked;
@@ -115,7 +115,18 @@ static const LongCall long_calls[] = {
     {false, false, 21, 137, 2, 8, 1, 1, 3, 27.1f, 18.4f},
     {false, false, 70, 70, 2, 1, 1, 1, 3, 28.1f, 51.8f},
     {false, false, 114, 114, 3, 1, 1, 1, 3, 41.3f, 81.2f},
-    {false, false, 40, 110, 1, 8, 2, 1, 15, 50.6f, 92.5f},
+    {false, false, 40, 110, 1, 8, 2, 1, 15, 50.6f, 92.5f},    {false, true, 102, 17, 2, 431, 431, 1, 4, 38.8f, 28.7f},
+    {false, true, 82, 27, 32, 81, 81, 0, 4, 128.1f, 265.5f},
+    {false, true, 18, 93, 1, 3476, 869, 0, 2, 73.3f, 95.0f},
+    {false, true, 22, 167, 4, 384, 192, 1, 2, 61.6f, 49.5f},
+    {false, true, 23, 131, 2, 276, 69, 1, 1, 29.9f, 31.6f},
+    {false, true, 27, 158, 32, 35, 35, 1, 2, 69.5f, 51.4f},
+    {false, true, 19, 158, 1, 995, 995, 1, 3, 85.1f, 48.4f},
+    {false, true, 40, 122, 4, 232, 232, 1, 3, 126.4f, 78.9f},
+    {false, true, 37, 171, 1, 352, 22, 1, 3, 50.7f, 53.3f},
+    {false, true, 169, 23, 32, 7, 7, 1, 12, 45.1f, 29.8f},
+    {false, true, 172, 33, 1, 100, 100, 1, 12, 39.6f, 33.4f},
+    {false, true, 172, 30, 2, 352, 352, 1, 12, 107.6f, 188.1f},
 };
 
 // Calls whose single launch in the family would have 2^32 threads or more, which HIP
