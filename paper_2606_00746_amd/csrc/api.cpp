@@ -113,12 +113,14 @@ hipError_t dispatch_bwd(const Problem &p, hipStream_t s)
     if (tiny_supported(p))
         return launch_bwd_tiny(p, s);
     if (p.H <= kSmallSide && p.W <= kSmallSide) {
-        const bool plane = p.room(plane_bwd_bytes(p));
-        if (small_bwd_preferred(p))
+        const bool plane = p.room(plane_bwd_bytes(p)), small = p.room(small_bwd_bytes(p));
+        if (small && small_bwd_preferred(p))
             return launch_bwd_small(p, s);
         if (!(plane && plane_preferred(p, true)) && line_supported(p, true))
             return launch_bwd_line(p, s);
-        return plane ? launch_bwd_plane(p, s) : launch_bwd_small(p, s);
+        if (plane)
+            return launch_bwd_plane(p, s);
+        return !small && line_fits(p, true) ? launch_bwd_line(p, s) : launch_bwd_small(p, s);
     }
     if (line_supported(p, true))
         return launch_bwd_line(p, s);

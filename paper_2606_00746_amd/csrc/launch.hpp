@@ -106,6 +106,7 @@ constexpr int kLdsBytes = 160 * 1024;
 
 bool small_fwd_preferred(const Problem &p);
 bool small_bwd_preferred(const Problem &p);
+int64_t small_bwd_bytes(const Problem &p);
 hipError_t launch_fwd_small(const Problem &p, hipStream_t s);
 hipError_t launch_bwd_small(const Problem &p, hipStream_t s);
 // Planes of any type and layout with both sides up to kSmallSide: whole planes
@@ -164,6 +165,7 @@ hipError_t launch_fwd_wide_sum(const Problem &p, hipStream_t s);
 // Planes of any type and layout with both sides up to kLineSide (scan_line.hip).
 constexpr int kLineSide = 256;
 bool line_supported(const Problem &p, bool bwd);
+bool line_fits(const Problem &p, bool bwd);
 bool line_fwd_preferred(const Problem &p);
 hipError_t launch_fwd_line(const Problem &p, hipStream_t s);
 hipError_t launch_bwd_line(const Problem &p, hipStream_t s);

@@ -941,6 +941,7 @@ struct LinePlan {
     int64_t plane_lines, plane_copies, unit_bytes;
     int64_t bytes;                   // workspace taken
     bool fits;                       // a round of one group fits
+    bool worth;                      // its rounds are not too many
 };
 
 LinePlan line_plan(const Problem &p, bool bwd)
@@ -994,8 +995,8 @@ LinePlan line_plan(const Problem &p, bool bwd)
     const int64_t waves = q.ru * q.cpg * q.D * (bwd ? 2 : 1);
     const int steps = std::max(nv ? p.H : 0, q.nh ? p.W : 0);
     const int kind = p.layout != kPixelMajor ? 2 : (q.nh || q.rows_x ? 1 : 0);
-    q.fits = q.fits && (rounds == 1 || waves >= kFullWaves ||
-                        (bwd ? rounds <= kFewRounds : rounds * kRoundSteps[kind] <= steps));
+    q.worth = rounds == 1 || waves >= kFullWaves ||
+              (bwd ? rounds <= kFewRounds : rounds * kRoundSteps[kind] <= steps);
     q.bytes = std::max(gen, q.ru * q.unit_bytes + kPartPad);
     return q;
 }
@@ -1249,6 +1250,15 @@ bool line_supported(const Problem &p, bool bwd)
 {
     if (!bwd && p.layout != kPixelMajor && few_steps(p))
         return false;
+    if ((p.H > p.W ? p.H : p.W) > kLineSide)
+        return false;
+    const LinePlan q = line_plan(p, bwd);
+    return q.fits && q.worth;
+}
+
+// Whether the workspace holds a round of it at all.
+bool line_fits(const Problem &p, bool bwd)
+{
     return (p.H > p.W ? p.H : p.W) <= kLineSide && line_plan(p, bwd).fits;
 }
 

@@ -328,27 +328,44 @@ hipError_t fwd_small_t(const Problem &p, hipStream_t st)
     return hipGetLastError();
 }
 
+// The backward's split: `cw` channels a workgroup, `nchunk` workgroups a group.
+struct BwdSplit {
+    int cw, nchunk;                  // nchunk 0: no channel fits
+    size_t per_ch;                   // LDS bytes a channel
+};
+
+BwdSplit bwd_split(const Problem &p, int T)
+{
+    const int NL = 64 / T, pitch = p.W | 1, cpg = p.C / p.G;
+    BwdSplit q{0, 0, (size_t)p.H * pitch * 4 + 2 * 3 * T * 4};
+    int cap = (int)((size_t)kLdsBytes / q.per_ch);
+    cap = cap < 8 * NL ? cap : 8 * NL;
+    cap = cap / NL * NL;
+    if (cap < NL)
+        return q;
+    q.nchunk = (cpg + cap - 1) / cap;
+    q.cw = (cpg + q.nchunk - 1) / q.nchunk;
+    q.cw = (q.cw + NL - 1) / NL * NL;
+    return q;
+}
+
+int64_t dw_elems(const Problem &p)
+{
+    return (int64_t)__builtin_popcount(p.mask) * p.B * p.G * 3 * p.H * p.W;
+}
+
 template <int T, typename S>
 hipError_t bwd_small_t(const Problem &p, hipStream_t st)
 {
     constexpr int NL = 64 / T;
     hipError_t e = hipSuccess;
-    const int lds_max = kLdsBytes;
-    const int pitch = p.W | 1;
-    const size_t per_ch = (size_t)p.H * pitch * 4 + 2 * 3 * T * 4;
-    const int cpg = p.C / p.G;
-    int cap = (int)((size_t)lds_max / per_ch);
-    cap = cap < 8 * NL ? cap : 8 * NL;
-    cap = cap / NL * NL;
-    if (cap < NL)
+    const BwdSplit q = bwd_split(p, T);
+    const int cw = q.cw, nchunk = q.nchunk;
+    if (nchunk == 0)
         return hipErrorInvalidConfiguration;
-    const int nchunk = (cpg + cap - 1) / cap;
-    int cw = (cpg + nchunk - 1) / nchunk;
-    cw = (cw + NL - 1) / NL * NL;
     const int nwaves = cw / NL;
-    const size_t lds = (size_t)cw * per_ch;
-    const int D = __builtin_popcount(p.mask);
-    const int64_t ndw = (int64_t)D * p.B * p.G * 3 * p.H * p.W;
+    const size_t lds = (size_t)cw * q.per_ch;
+    const int64_t ndw = dw_elems(p);
 
     float *dwp = nullptr;
     if (nchunk > 1) {
@@ -487,6 +504,13 @@ bool small_bwd_preferred(const Problem &p)
     const int steps = std::max((p.mask & 3) ? p.H : 0, (p.mask & 12) ? p.W : 0);
     const bool few = __builtin_popcount(p.mask) == 1 ? HW <= 20 && m <= 16 : HW < 12 && m <= 5;
     return few && (int64_t)(p.C / p.G) * steps <= 64;
+}
+
+// Bytes of the backward's partial sums.
+int64_t small_bwd_bytes(const Problem &p)
+{
+    const int n = bwd_split(p, lanes_per_line(p.H, p.W)).nchunk;
+    return n > 1 ? n * dw_elems(p) * (int64_t)sizeof(float) : 0;
 }
 
 hipError_t launch_fwd_small(const Problem &p, hipStream_t st)

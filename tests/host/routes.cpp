@@ -4,6 +4,10 @@
 
 #include "launch.hpp"
 
+namespace gspn {
+hipError_t dispatch_bwd(const Problem &p, hipStream_t s);      // api.cpp
+}
+
 using namespace gspn;
 
 struct Call {
@@ -129,6 +133,35 @@ static const LongCall long_calls[] = {
     {false, true, 172, 30, 2, 352, 352, 1, 12, 107.6f, 188.1f},
 };
 
+// Whatever the workspace, a backward up to 64 a side that any family can run in it is
+// taken, and takes no more than it.
+static int check_limited()
+{
+    int bad = 0;
+    Workspace ws;
+    ws.counting = true;
+    for (int side : {1, 3, 9, 17, 20, 33, 38, 63})
+        for (int cpg : {1, 7, 40, 60, 130})
+            for (int G : {1, 6})
+                for (int mask : {1, 12, 15})
+                    for (int layout : {kBlocked, kPixelMajor})
+                        for (int64_t cap = 0; cap < (int64_t)1 << 30; cap = cap * 3 / 2 + 1024) {
+                            Problem p{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                                      nullptr, nullptr, nullptr, mask, 2, cpg * G, G, side, side + 1, 1,
+                                      layout, &ws};
+                            ws.used = 0;
+                            p.ws_cap = cap;
+                            const bool can = small_bwd_bytes(p) <= cap || plane_bwd_bytes(p) <= cap ||
+                                             line_fits(p, true);
+                            if (dispatch_bwd(p, nullptr) != hipSuccess || (can && (int64_t)ws.used > cap)) {
+                                printf("%dx%d cpg %d G %d mask %d layout %d: %lld of %lld bytes\n", side,
+                                       side + 1, cpg, G, mask, layout, (long long)ws.used, (long long)cap);
+                                ++bad;
+                            }
+                        }
+    return bad;
+}
+
 // Calls whose single launch in the family would have 2^32 threads or more, which HIP
 // refuses, and the largest that have fewer: taken by the family or not.
 static int check_launch_limits()
@@ -158,7 +191,7 @@ static int check_launch_limits()
 
 int main()
 {
-    int bad = check_launch_limits();
+    int bad = check_launch_limits() + check_limited();
     for (const LongCall &c : long_calls) {
         Problem p{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                   nullptr, c.mask, c.B, c.C, c.G, c.H, c.W, c.dtype, c.blocked ? kBlocked : kPixelMajor};
