@@ -98,7 +98,9 @@ hipError_t dispatch_fwd(const Problem &p, hipStream_t s)
             return launch_fwd_small(p, s);
         if (plane_preferred(p, false))
             return launch_fwd_plane(p, s);
-        return line_supported(p, false) ? launch_fwd_line(p, s) : launch_fwd_small(p, s);
+        if (line_supported(p, false))
+            return launch_fwd_line(p, s);
+        return plane_over_small(p) ? launch_fwd_plane(p, s) : launch_fwd_small(p, s);
     }
     const bool wide = wide_supported(p) && (p.ws_cap < 0 || p.room(wide_fwd_bytes(p)));
     if ((!wide || line_fwd_preferred(p)) && line_supported(p, false))

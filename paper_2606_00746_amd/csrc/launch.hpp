@@ -112,6 +112,7 @@ hipError_t launch_bwd_small(const Problem &p, hipStream_t s);
 // Planes of any type and layout with both sides up to kSmallSide: whole planes
 // in LDS (scan_plane.hip).
 bool plane_preferred(const Problem &p, bool bwd);
+bool plane_over_small(const Problem &p);
 int plane_channels(const Problem &p, bool bwd);
 int64_t plane_bwd_bytes(const Problem &p);
 hipError_t launch_fwd_plane(const Problem &p, hipStream_t s);

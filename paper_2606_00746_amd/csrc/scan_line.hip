@@ -914,15 +914,28 @@ constexpr int64_t kPartPad = 64 * 256;           // alignment of a round's parts
 // own launches and its own chain of steps.  They are taken where a round still
 // has two waves a CU, or where there are so few of them that all planes at once in
 // the general family, whose time is its steps, take longer: in the backward up to
-// kFewRounds; in the forward one for so many steps (kRoundSteps: vertical
+// kFewRounds, or in proportion to the channels of a group, which the general
+// backward takes in turn; in the forward one for so many steps (kRoundSteps: vertical
 // pixel-major directions alone, which turn nothing around; pixel-major; blocked,
-// where every tensor of a direction is a launch).  us, rounds / general: T2B and B2T,
+// where every tensor of a direction is a launch), a step counted by `load`, the time of
+// all planes' general step over that of a few: it grows with their lines, horizontal
+// ones, which it reads by columns, most.  us, rounds / general: T2B and B2T,
 // 70 x 70, two rounds: 28 / 52, 114 x 114, three: 41 / 81, 21 x 137, two: 27 / 18;
 // 62 x 88, two, four directions: 45 / 81, 22 x 145, four, R2L: 151 / 93; blocked 77
-// x 77, 8, four directions: 159 / 60, 28 x 154, four: 230 / 97.
+// x 77, 8, four directions: 159 / 60, 28 x 154, four: 230 / 97; 51 x 73, L2R, B*C =
+// 1448, rounds below that: 144 / 633; blocked 114 x 114, both horizontal, 366: 176 / 248.
+//
+// The blocked forward, whose rounds have the most launches, and planes up to 64 a side,
+// whose other families' backward is faster than the general one, ask for more waves (a workspace
+// below the query's; us, rounds / the other family): blocked 35 x 149, four
+// directions, three rounds of 1376: 393 / 277; backward 38 x 38, T2B and B2T, seven of
+// 1088: 322 / 175, blocked eleven of 704: 847 / 180, 42 x 64, four directions, eleven of
+// 1664: 1857 / 1032, but pixel-major ten of 1920: 859 / 1929, 63 x 63, three, ten of 672:
+// 589 / 775; fp32 42 x 23, four, twelve of 2304: 2026 / 683, bf16 31 x 31, four: 1980 /
+// 453.
 constexpr int64_t kFullWaves = 512;
 constexpr int64_t kFewRounds = 4;
-constexpr int kRoundSteps[3] = {16, 37, 60};
+constexpr int kRoundSteps[3] = {16, 38, 50};
 
 // What a call of the general family takes; planes of at most 64 have other
 // fallbacks, which take less.
@@ -940,6 +953,7 @@ struct LinePlan {
     int64_t units, ru;               // units (b, g), units per round
     int64_t plane_lines, plane_copies, unit_bytes;
     int64_t bytes;                   // workspace taken
+    int64_t rounds;
     bool fits;                       // a round of one group fits
     bool worth;                      // its rounds are not too many
 };
@@ -979,6 +993,7 @@ LinePlan line_plan(const Problem &p, bool bwd)
                    (q.nchunk > 1 ? (int64_t)q.nchunk * q.D * 3 * p.H * p.W * 4 : 0);
     const int64_t gen = general_bytes(p, bwd), one = q.unit_bytes + kPartPad;
     int64_t most = std::max({gen, kRoundBytes, one});
+    const int64_t whole = most;
     if (p.ws_cap >= 0)
         most = std::min(most, p.ws_cap - (((int64_t)p.ws->used + 255) & ~(int64_t)255));
     else if (gen > 0 && gen < kSmallBytes && (bwd || !wide_supported(p)))
@@ -991,12 +1006,24 @@ LinePlan line_plan(const Problem &p, bool bwd)
     q.fits = q.fits && q.cpg <= max_planes;
     q.ru = std::max<int64_t>(1, std::min(q.ru, max_planes / q.cpg));
     // rounds follow each other on the stream
-    const int64_t rounds = (q.units + q.ru - 1) / q.ru;
+    q.rounds = (q.units + q.ru - 1) / q.ru;
     const int64_t waves = q.ru * q.cpg * q.D * (bwd ? 2 : 1);
     const int steps = std::max(nv ? p.H : 0, q.nh ? p.W : 0);
-    const int kind = p.layout != kPixelMajor ? 2 : (q.nh || q.rows_x ? 1 : 0);
-    q.worth = rounds == 1 || waves >= kFullWaves ||
-              (bwd ? rounds <= kFewRounds : rounds * kRoundSteps[kind] <= steps);
+    const bool blocked = p.layout != kPixelMajor;
+    const int kind = blocked ? 2 : (q.nh || q.rows_x ? 1 : 0);
+    int64_t full = kFullWaves;
+    if (most < whole && m <= kSmallSide && bwd)
+        full *= blocked || m <= 32 || p.dtype == 0 ? 8 : q.D <= 2 ? 4 : 1;
+    else if (most < whole && blocked && !bwd)
+        full *= 8;
+    // the general forward's load and the line family's turned planes, in tenths of a step
+    const int64_t planes = (int64_t)p.B * p.C, hl = planes * q.nh * p.H, vl = planes * nv * p.W;
+    const int64_t by_load = blocked ? (4 * hl + vl) / 10000 : (5 * hl + vl) / 4600;
+    const int64_t load = kind == 0 ? 10 : std::max<int64_t>(10, by_load);
+    const int64_t turned = blocked ? planes * p.H * p.W * q.D / 9000 : 0;
+    const int64_t few = std::max<int64_t>(kFewRounds, m <= kSmallSide ? 0 : (blocked ? 2 : 3) * q.cpg);
+    q.worth = q.rounds == 1 || waves >= full ||
+              (bwd ? q.rounds <= few : 10 * q.rounds * kRoundSteps[kind] + turned <= steps * load);
     q.bytes = std::max(gen, q.ru * q.unit_bytes + kPartPad);
     return q;
 }
@@ -1267,10 +1294,12 @@ bool line_fits(const Problem &p, bool bwd)
 // and plane beats a workgroup per plane (us, wide / line): 128 x 128, B*C =
 // 384: 121 / 91, 2048: 583 / 481; 72 x 72, 2048: 295 / 213; 256 x 256, 8: 96 /
 // 66, 64: 119 / 83; but 256: 240 / 251, 1024: 958 / 1024; 160 x 160, 1024: 407
-// / 491 (4 positions a lane move more bytes than the wide family's rounds).
+// / 491 (4 positions a lane move more bytes than the wide family's rounds).  In a
+// workspace that holds the wide family's only in one round: 160 x 184 T2B, B*C = 160,
+// two: 49 / 80; 104 x 104, T2B and B2T, 96, two: 36 / 45.
 bool line_fwd_preferred(const Problem &p)
 {
-    return p.layout == kPixelMajor &&
+    return p.layout == kPixelMajor && (p.ws_cap < 0 || line_plan(p, false).rounds == 1) &&
            ((p.H <= 128 && p.W <= 128) ||
             (int64_t)__builtin_popcount(p.mask) * p.B * p.C <= 512);
 }

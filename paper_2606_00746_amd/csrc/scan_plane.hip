@@ -793,6 +793,23 @@ bool plane_preferred(const Problem &p, bool bwd)
            wgs >= (one ? 28 : 128) && (horizontal || wgs * q.nwaves >= 600);
 }
 
+// Forwards that would be the line family's, without the workspace for it: plane
+// against the small kernels, which both take none (us, small / plane: fp32 43 x 43,
+// both horizontal, B*C = 1344: 274 / 50; bf16 36 x 56, T2B and B2T, 856: 34 / 18; 59 x
+// 56, four, 49: 32 / 66, 59 x 59, both horizontal, 288: 144 / 71; fp32 62 x 62, four, one
+// channel a CU, 508: 155 / 238; blocked fp32 33 x 62, 3 channels a CU, 768: 70 / 110).
+bool plane_over_small(const Problem &p)
+{
+    const PlanePlan q = plane_plan_of(p, false);
+    if (q.nchunk == 0)
+        return false;
+    const int64_t w = (int64_t)p.B * p.C * q.T / 64;
+    const bool pm = p.layout == kPixelMajor;
+    const int ch = plane_channels(p, false);
+    return (w >= 400 && ch >= (pm ? 3 : 4)) ||
+           (pm && ch >= 2 && w * __builtin_popcount(p.mask & 12) >= 500);
+}
+
 // Bytes of the backward's partial sums.
 int64_t plane_bwd_bytes(const Problem &p)
 {

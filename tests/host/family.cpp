@@ -21,7 +21,7 @@ static const char *family(const Problem &p, bool bwd)
             return "small";
         if (plane_preferred(p, bwd))
             return "plane";
-        return line_supported(p, bwd) ? "line" : bwd ? "plane" : "small";
+        return line_supported(p, bwd) ? "line" : bwd || plane_over_small(p) ? "plane" : "small";
     }
     const bool wide = !bwd && wide_supported(p);
     if ((!wide || line_fwd_preferred(p)) && line_supported(p, bwd))

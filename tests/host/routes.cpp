@@ -133,6 +133,29 @@ static const LongCall long_calls[] = {
     {false, true, 172, 30, 2, 352, 352, 1, 12, 107.6f, 188.1f},
 };
 
+// A caller's workspace below the query's: line family in rounds / the other family.
+struct LimitedCall {
+    bool bwd, blocked;
+    int H, W, B, C, G, dtype, mask;
+    int64_t bytes;
+    float line, other;
+};
+
+static const LimitedCall limited_calls[] = {
+    {true, true, 38, 38, 1, 1856, 116, 1, 3, 8040192, 847.3f, 179.5f},
+    {true, true, 54, 54, 1, 1808, 113, 1, 15, 31632768, 1714.6f, 584.3f},
+    {true, false, 38, 38, 1, 1856, 116, 1, 3, 8040192, 321.8f, 174.5f},
+    {true, false, 59, 34, 2, 992, 62, 1, 3, 11939712, 349.4f, 265.5f},
+    {true, false, 63, 63, 4, 272, 17, 1, 7, 19432224, 589.2f, 775.5f},
+    {true, false, 42, 64, 2, 1104, 69, 1, 15, 35610624, 859.2f, 1928.7f},
+    {true, false, 42, 23, 4, 832, 26, 0, 15, 19289088, 2026.0f, 683.4f},
+    {true, false, 31, 31, 1, 3264, 102, 1, 15, 9410112, 1979.7f, 453.4f},
+    {false, false, 51, 73, 8, 181, 181, 1, 8, 21563616, 143.6f, 633.4f},
+    {false, true, 83, 83, 32, 12, 4, 1, 15, 42326016, 205.3f, 160.1f},
+    {false, false, 83, 83, 32, 12, 4, 1, 15, 42326016, 89.6f, 590.1f},
+    {true, true, 35, 149, 1, 708, 177, 1, 15, 118151040, 665.6f, 1982.0f},
+};
+
 // Whatever the workspace, a backward up to 64 a side that any family can run in it is
 // taken, and takes no more than it.
 static int check_limited()
@@ -140,6 +163,16 @@ static int check_limited()
     int bad = 0;
     Workspace ws;
     ws.counting = true;
+    for (const LimitedCall &c : limited_calls) {
+        Problem p{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                  nullptr, c.mask, c.B, c.C, c.G, c.H, c.W, c.dtype, c.blocked ? kBlocked : kPixelMajor, &ws};
+        p.ws_cap = c.bytes;
+        if (line_supported(p, c.bwd) != (c.line < c.other)) {
+            printf("limited %s%s %dx%d C=%d: line %.1f, other %.1f us\n", c.bwd ? "bwd" : "fwd",
+                   c.blocked ? "_blocked" : "", c.H, c.W, c.C, c.line, c.other);
+            ++bad;
+        }
+    }
     for (int side : {1, 3, 9, 17, 20, 33, 38, 63})
         for (int cpg : {1, 7, 40, 60, 130})
             for (int G : {1, 6})

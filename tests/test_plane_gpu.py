@@ -176,11 +176,14 @@ def test_infinite_adjoint_at_a_lines_end(wl):
                               np.take(clean[k], others, axis=axis)), k
 
 
-def test_caller_without_workspace():
+@pytest.mark.parametrize("wl", [case("no-workspace-50x64", 1, 8, 1, 50, 64),
+                                case("no-workspace-43x30-dirs12", 2, 126, 42, 43, 30, dirs=12)],
+                         ids=lambda w: w.name)
+def test_caller_without_workspace(wl):
     """A backward whose groups now split over more workgroups than its query
-    once sized (or lines go through memory) still runs in no workspace."""
+    once sized (or lines go through memory) still runs in no workspace, and so
+    does the forward, in the plane family for many planes."""
     torch = require_gpu()
-    wl = case("no-workspace-50x64", 1, 8, 1, 50, 64)
     print(f"[case] {wl.name}", flush=True)
     inputs = gi.make_inputs(wl, with_dy=True)
     t = upload(inputs, wl.dtype, wl.dirs)
