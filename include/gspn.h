@@ -71,10 +71,11 @@
  * fp32 lines and turned copies there: their size may be several times that of
  * the tensors, up to 512 MB, or what one weight group or the kernels that need
  * less take where that is more.  They run with less too, in smaller parts (the
- * same results bit for bit) or on kernels that need less: above 64 a side the fp32 planes of gspn_scan_fwd's directions
- * or the backward's partial sums, up to 64 a side nothing or the latter (their
- * results agree within the rounding of fp32).  What the kernels that need the
- * least take is accepted, and the query gives no more where that is below 704 KB.
+ * same results bit for bit) or on kernels that need less: above 64 a side the
+ * fp32 planes of gspn_scan_fwd's directions or the backward's partial sums, up to
+ * 64 a side nothing or the latter (their results agree within the rounding of
+ * fp32).  What the kernels that need the least take is accepted, and the query
+ * gives no more where that is below 704 KB.
  * The workspace's contents on entry do not matter and are undefined after the
  * call; calls that share a workspace must not run
  * concurrently.
